@@ -13,8 +13,9 @@ A case is a dict of plain values:
   free, tm, tempered, split    standardized form: free spectra, columns of a
             stored design matrix (0: offset and quadratic), a temperature
             ladder, split common-process / pulsar-noise coefficients
-  tiles, waves, place          tuning of the TOA pass; tiles 0 takes the one a
-            server takes, tiles -1 leaves the data set's default
+  tiles, waves, place          tuning of the TOA pass; tiles 0 takes the chunk
+            length that fits the data set (with one wave a workgroup as a
+            server does), tiles -1 leaves the data set's default
 
 Data are drawn from the seed: pulsars uniform on the sky, ragged TOA counts,
 uncertainties of 10^-6 s within a decade or so, one to four backends per
@@ -53,12 +54,13 @@ def listed():
         # A whole trajectory of many chains on a small array.
         _case(name="toa_hmc_3psr_256chains", form="toa", call="hmc", n_psr=3, n_toa=1500, chains=256, leapfrog=20),
         # One evaluation of the benchmark's array (67 pulsars, 250k TOAs, 64
-        # chains) at the tuning that the autotuner finds there.
+        # chains), with workgroups of four waves that fill one round of the
+        # device: what the autotuner finds there.
         _case(name="toa_eval_67psr_64chains", form="toa", call="eval", n_psr=67, n_toa=250_000, nf_rn=30, nf_gw=14,
-              nf_dm=30, chains=64, tiles=96, waves=4, place=2),
+              nf_dm=30, chains=64, tiles=0, waves=4, place=2),
         # A whole trajectory of it: the benchmark's own step.
         _case(name="toa_hmc_67psr_64chains", form="toa", call="hmc", n_psr=67, n_toa=250_000, nf_rn=30, nf_gw=14,
-              nf_dm=30, chains=64, leapfrog=20, tiles=96, waves=4, place=2),
+              nf_dm=30, chains=64, leapfrog=20, tiles=0, waves=4, place=2),
         # A served request with a continuous wave, 16 chains as the server runs it.
         _case(name="toa_eval_cw_45psr_16chains", form="toa", call="eval", n_psr=45, n_toa=60_001, nf_rn=17, nf_gw=17,
               nf_dm=17, cw=True, chains=16, tiles=0),
@@ -228,8 +230,15 @@ def prepare(case, seed):
              beta=None if beta is None else torch.tensor(beta, device="cuda"))
     if case["form"] == "toa" and case["tiles"] >= 0:
         cu = torch.cuda.get_device_properties(0).multi_processor_count
-        g.ptafs_set_tuning(*((case["tiles"], case["waves"], case["place"]) if case["tiles"] else
-                             autotune.serving_tuning(d["toa_offsets"], case["chains"], cu)))
+        if case["tiles"]:
+            tuning = case["tiles"], case["waves"], case["place"]
+        elif case["waves"] == 1:
+            tuning = autotune.serving_tuning(d["toa_offsets"], case["chains"], cu)
+        else:
+            fit = autotune.round_fitting_tpcs(d["toa_offsets"], case["chains"], cu, wpb=case["waves"], rounds=(1,),
+                                              waves_per_simd=(2,))
+            tuning = fit[0], case["waves"], case["place"]
+        g.ptafs_set_tuning(*tuning)
     if case["call"] == "autograd":
         s["x"].requires_grad_(True)
     if case["call"] == "hmc":
