@@ -34,120 +34,24 @@
 // with pi(c) = 4 (c mod 4) + c / 4, so that lane group q of a result holds the
 // consecutive rows 4q .. 4q + 3 of every tile.
 #include "common.h"
+#include "lane_dev.h"
 #include "spec_dev.h"
 
 namespace {
 
 using pt::Dev;
 using pt::pk;
-using v4d = double __attribute__((ext_vector_type(4)));
-
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ inline double readlane_d(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// 1/sqrt(a): hardware estimate refined by two Newton steps
-__device__ inline double rsqrt_nr(double a) {
-  double y = __builtin_amdgcn_rsq(a);
-  y = y * (1.5 - 0.5 * a * y * y);
-  y = y * (1.5 - 0.5 * a * y * y);
-  return y;
-}
-
-// 1/a: hardware estimate refined by two Newton steps on e = 1 - a y
-__device__ inline double rcp_nr(double a) {
-  double y = __builtin_amdgcn_rcp(a);
-  y = fma(y, fma(-a, y, 1.0), y);
-  y = fma(y, fma(-a, y, 1.0), y);
-  return y;
-}
-
-template <int N>
-__device__ inline int dpp_row_share(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x150 + N, 0xF, 0xF, false);
-}
-
-// Lane n of every 16-lane row to all lanes of that row (DPP row broadcast);
-// n is a constant once the caller's loop is unrolled.
-__device__ inline double row_share_d(double v, int n) {
-  const long long b = __double_as_longlong(v);
-  int lo = (int)b, hi = (int)(b >> 32);
-  switch (n) {
-#define PT_ROW_SHARE(N)          \
-  case N:                        \
-    lo = dpp_row_share<N>(lo);   \
-    hi = dpp_row_share<N>(hi);   \
-    break;
-    PT_ROW_SHARE(0) PT_ROW_SHARE(1) PT_ROW_SHARE(2) PT_ROW_SHARE(3)
-    PT_ROW_SHARE(4) PT_ROW_SHARE(5) PT_ROW_SHARE(6) PT_ROW_SHARE(7)
-    PT_ROW_SHARE(8) PT_ROW_SHARE(9) PT_ROW_SHARE(10) PT_ROW_SHARE(11)
-    PT_ROW_SHARE(12) PT_ROW_SHARE(13) PT_ROW_SHARE(14) PT_ROW_SHARE(15)
-#undef PT_ROW_SHARE
-  }
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Row g (lanes 16g .. 16g + 15) to all four rows, lane for lane: a permlane16
-// swap gives rows (g mod 2) and 2 + (g mod 2) twice each, a permlane32 swap
-// then the chosen one four times.
-__device__ inline unsigned row_bcast_u(unsigned v, int g) {
-  const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  const unsigned y = (g & 1) ? p[1] : p[0];
-  const auto r = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-  return (g & 2) ? r[1] : r[0];
-}
-
-__device__ inline double row_bcast_d(double v, int g) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = row_bcast_u((unsigned)b, g), hi = row_bcast_u((unsigned)(b >> 32), g);
-  return __longlong_as_double(((long long)hi << 32) | lo);
-}
-
-// v of the same lane in the partner row (row q ^ 1, by the permlane16 swap)
-// and in the partner half (row q ^ 2, by the permlane32 swap), q the caller's
-// row: the swaps give every lane the value of the lower and of the upper
-// member of its pair.
-__device__ inline double xor16_d(double v, int q) {
-  const long long b = __double_as_longlong(v);
-  const auto pl = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
-  const auto ph = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  const unsigned lo = (q & 1) ? pl[0] : pl[1], hi = (q & 1) ? ph[0] : ph[1];
-  return __longlong_as_double(((long long)hi << 32) | lo);
-}
-__device__ inline double xor32_d(double v, int q) {
-  const long long b = __double_as_longlong(v);
-  const auto pl = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
-  const auto ph = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
-  const unsigned lo = (q & 2) ? pl[0] : pl[1], hi = (q & 2) ? ph[0] : ph[1];
-  return __longlong_as_double(((long long)hi << 32) | lo);
-}
-
-// The same through the LDS crossbar: every lane reads lane addr / 4 (addr =
-// 4 (c + 16 g) for row g), two DS instructions instead of the VALU swaps.
-__device__ inline double bperm_bcast_d(double v, int addr) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)b);
-  const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// acc += X Y for one 16x16x16 product given the four k-slices of both operands
-__device__ inline v4d mfma4(const v4d &a, const v4d &b, v4d acc) {
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2], b[2], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[3], b[3], acc, 0, 0, 0);
-  return acc;
-}
+using ln::bperm_bcast_d;
+using ln::mfma4;
+using ln::rcp_nr;
+using ln::readlane_d;
+using ln::row_bcast_d;
+using ln::row_share_d;
+using ln::rsqrt_nr;
+using ln::v4d;
+using ln::wave_sync;
+using ln::xor16_d;
+using ln::xor32_d;
 
 __host__ __device__ constexpr int tidx(int I, int J) { return I * (I + 1) / 2 + J; }
 

@@ -29,384 +29,60 @@
 // parameters through S_D, Q_D, e_D, the transform of the samples and the
 // waveform's derivative.
 //
-// Matrices live in LDS as lower 16x16 tiles (row-major inside).  The
-// factorisation is right-looking by block columns: a diagonal tile is factorised
-// and inverted by one wave (lane r holds row r, operands by readlane), the
-// panel and the trailing tiles are updated on FP64 matrix cores
-// (v_mfma_f64_16x16x4f64), and X = L^-1 follows by block forward substitution,
-// also on matrix cores.  MFMA operand convention (lane l = c + 16 q): slice s of
-// a 16x16x16 product takes A[c][q + 4s] and B[q + 4s][c] (reduction index
-// q + 4s); the result holds R[q + 4v][c] in register v (the row of the A
-// operand's lane q + 4v), which is directly the B operand of a next product.
+// X = L~^-1 is formed by block Gauss-Jordan elimination with the matrix in the
+// registers of one to four waves (elim_dev.h), which carries t = X beta d~ and
+// L~ z~ along.  What bounds it: at 67 pulsars x 64 chains (T = 8) the products of
+// a problem take 57e3 cycles of a matrix core, a quarter of that on each of the
+// four SIMDs, and the vector instructions around them (half of them in the
+// diagonal tiles) as long again on the FP64 pipe they share; k_std_fwd<8> runs
+// at 41% of the matrix cores' cycles.  The earlier form, with the tiles in LDS
+// (two problems a compute unit, every operand and result through LDS), took 525 us
+// a launch where this takes 320, 335 where this takes 84 at 100 pulsars with
+// T = 4, and k_split_fac<8> 466 where this takes 297.
 #include <cmath>
 
 #include "cw_dev.h"
+#include "elim_dev.h"
 #include "std.h"
 
 namespace {
 
 using ps::StdDev;
-using v4d = double __attribute__((ext_vector_type(4)));
+using ln::v4d;
 
-__device__ inline double readlane_d(double v, int lane) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
+// Waves per (pulsar, chain) or (frequency, chain) elimination of T tiles, and the
+// waves a SIMD that its registers are held to.  A wave takes at most 15 tiles
+// (120 of its registers); more waves shorten a step and cost barriers and issue.
+// Measured for 1600 problems, us: T = 6 with 2 waves 83, with 3 76; T = 7 with 2
+// waves 115, 3 104, 4 106 (its first wave's chain 33 and 28); T = 5 for 4288
+// problems, 1 wave 95 and 2 waves 105; T = 4 for 6400, 1 wave 75, 2 waves 91;
+// T = 8 for 4288, 3 waves at four problems a compute unit 346, 4 waves at three
+// 310, at four (with register spills) 390.
+template <int T>
+constexpr int elim_waves() { return T <= 5 ? 1 : T == 6 ? 3 : 4; }
+template <int T>
+constexpr int elim_occ() { return T <= 2 ? 4 : T == 5 ? 2 : 3; }
 
-// 1/sqrt(a) and 1/a: hardware estimates refined by two Newton steps
-__device__ inline double rsqrt_nr(double a) {
-  double y = __builtin_amdgcn_rsq(a);
-  y = y * (1.5 - 0.5 * a * y * y);
-  y = y * (1.5 - 0.5 * a * y * y);
-  return y;
-}
-__device__ inline double rcp_nr(double a) {
-  double y = __builtin_amdgcn_rcp(a);
-  y = fma(y, fma(-a, y, 1.0), y);
-  y = fma(y, fma(-a, y, 1.0), y);
-  return y;
-}
-
-// LDS tiles are row-major with the column index XOR-ed with the row index,
-// element (r, c) at 16 r + (c ^ r): the 16 lanes that read one column (a row
-// each), or one row (a column each), or an MFMA operand, hit 16 different
-// banks.
-__device__ inline int sw(int r, int c) { return (r << 4) + (c ^ r); }
-
-// Tile loads for the MFMA operands (see the convention above).
-__device__ inline v4d ld_rm(const double *t, int c, int q) {   // Y[c][q+4s]: A of Y, B of Y^T
-  return v4d{t[sw(c, q)], t[sw(c, q + 4)], t[sw(c, q + 8)], t[sw(c, q + 12)]};
-}
-__device__ inline v4d ld_cm(const double *t, int c, int q) {   // Y[q+4s][c]: B of Y, result of Y
-  return v4d{t[sw(q, c)], t[sw(q + 4, c)], t[sw(q + 8, c)], t[sw(q + 12, c)]};
-}
-__device__ inline void st_cm(double *t, int c, int q, v4d v) {
-  t[sw(q, c)] = v[0];
-  t[sw(q + 4, c)] = v[1];
-  t[sw(q + 8, c)] = v[2];
-  t[sw(q + 12, c)] = v[3];
-}
-// the same from a plain row-major tile in global memory
+// the plain row-major tile t of global memory as an MFMA B operand
 __device__ inline v4d ldg_cm(const double *t, int c, int q) {
   const double *p = t + 16 * q + c;
   return v4d{p[0], p[64], p[128], p[192]};
 }
-__device__ inline v4d mma(v4d a, v4d b, v4d acc) {
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2], b[2], acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[3], b[3], acc, 0, 0, 0);
-  return acc;
-}
 
-// Keeps a register row computed here: the updates before it happen before the
-// loads after it (no load is hoisted above, no update sunk below).
-__device__ inline void pin_row(double (&v)[16]) {
+// Block sum of one value per thread (W waves); every thread gets the sum.
+template <int W>
+__device__ inline double wave_block_sum(double v, double *red) {
 #pragma unroll
-  for (int k = 0; k < 16; ++k) asm volatile("" : "+v"(v[k]));
-  asm volatile("" ::: "memory");
-}
-
-// A pointer into LDS that stays one (DS instructions, not flat ones).
-using lds_dp = __attribute__((address_space(3))) double *;
-
-__device__ inline void wave_sync() {   // LDS writes of the wave visible to its later reads
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Cholesky factor of the symmetric 16x16 tile t (both triangles present), in
-// place in the lower triangle (the upper one is left undefined).  Executed by
-// one wave; lane r holds row r.  Right-looking: pivot j's multipliers reach
-// rows j + 1 and j + 2 at once by readlane, the other rows through an LDS copy
-// of column j (bc, three buffers of 16) read two pivots later, when the store
-// has long completed (a wave's LDS accesses are executed in order).  idg
-// receives 1 / L_jj.  With LZ, lzJ[r] += sum_c L_rc zJ[c].  Returns false in
-// every lane when a pivot is not positive and finite.
-template <bool LZ>
-__device__ __forceinline__ bool diag_factor(double *t, lds_dp bc, lds_dp idg, int lane, const double *zJ,
-                                            double *lzJ) {
-  const int r = lane & 15;
-  double row[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[c] = t[sw(r, c)];
-  bool ok = true;
-  double l1 = 0.0, l2 = 0.0;   // this lane's multipliers of the two previous pivots
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const double piv = readlane_d(row[j], j);
-    double bv[16];
-    const bool def = (j >= 2) && (j <= 14);   // pivot j - 2 still owes rows j + 1 ...
-    if (def) {
-      const auto bp = bc + 16 * ((j - 2) % 3);
-#pragma unroll
-      for (int k = j + 1; k < 16; ++k) bv[k] = bp[k];
-    }
-    ok = ok && (piv > 0.0) && isfinite(piv);
-    const double rs = rsqrt_nr(piv);
-    const double l = row[j] * rs;       // L[r][j] (r >= j)
-    row[j] = l;
-    // the next pivot's column first (the path from pivot to pivot), then the rest
-    if (j + 1 < 16) {
-      if (def) row[j + 1] = fma(-l2, bv[j + 1], row[j + 1]);
-      row[j + 1] = fma(-l, readlane_d(l, j + 1), row[j + 1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (def) {
-#pragma unroll
-      for (int k = j + 2; k < 16; ++k) row[k] = fma(-l2, bv[k], row[k]);
-    }
-    if (j + 2 < 16) row[j + 2] = fma(-l, readlane_d(l, j + 2), row[j + 2]);
-    pin_row(row);   // the updates before the stores: a wait for the loads then
-                    // does not also wait for the stores (LDS completes in order)
-    if (j <= 12 && lane < 16) bc[16 * (j % 3) + r] = l;
-    if (lane == 0) idg[j] = rs;
-    l2 = l1;
-    l1 = l;
-    asm volatile("" ::: "memory");
-  }
-  if (lane < 16) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c)
-      if (c <= r) t[sw(r, c)] = row[c];
-    if (LZ) {
-      double s = 0.0;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) s = fma((c <= r) ? row[c] : 0.0, zJ[c], s);
-      lzJ[r] += s;
-    }
-  }
-  return ok;
-}
-
-// The lower-triangular tile t (L, upper triangle undefined) replaced by
-// X = L^-1 (zeros above); idg = 1 / L_jj.  Executed by one wave: lane c < 16
-// solves L x = e_c for column c, x_m = (delta_mc - sum_{k<m} L_mk x_k) / L_mm,
-// with L read from the tile at the same address in every lane.  Column m + 1
-// of L is loaded while column m is applied; the solve and the stores sit in
-// one branch so that the wave's loads all precede its stores.
-__device__ __forceinline__ void diag_inverse(double *t, lds_dp idg, int lane) {
-  const int r = lane & 15;
-  if (lane < 16) {
-    double acc[16], xc[16], lc[2][16], dg[2];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) acc[m] = 0.0;
-    dg[0] = idg[0];
-#pragma unroll
-    for (int k = 1; k < 16; ++k) lc[0][k] = t[sw(k, 0)];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int b = m & 1;
-      if (m < 15) {
-        dg[b ^ 1] = idg[m + 1];
-#pragma unroll
-        for (int k = m + 2; k < 16; ++k) lc[b ^ 1][k] = t[sw(k, m + 1)];
-      }
-      const double xm = (((m == r) ? 1.0 : 0.0) - acc[m]) * dg[b];
-      xc[m] = xm;
-#pragma unroll
-      for (int k = m + 1; k < 16; ++k) acc[k] = fma(lc[b][k], xm, acc[k]);
-      pin_row(acc);
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m) t[sw(m, r)] = (m >= r) ? xc[m] : 0.0;
-  }
-}
-
-// Row r of a panel tile: L_IJ = A_IJ L_JJ^-T by substitution,
-// x_c = (a_c - sum_{k<c} x_k L_ck) / L_cc, one row per thread, L_JJ (lower)
-// read at the same address by every lane.  With LZ, lzI[r] += sum_c x_c zJ[c].
-template <bool LZ>
-__device__ __forceinline__ void panel_row(double *t, const double *ljj, lds_dp idg, int r,
-                                          const double *zJ, double *lzI) {
-  double x[16], lc[2][16], dg[2];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) x[c] = t[sw(r, c)];
-  dg[0] = idg[0];
-#pragma unroll
-  for (int k = 1; k < 16; ++k) lc[0][k] = ljj[sw(k, 0)];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int b = c & 1;
-    if (c < 15) {   // column c + 1 of L_JJ while column c is applied
-      dg[b ^ 1] = idg[c + 1];
-#pragma unroll
-      for (int k = c + 2; k < 16; ++k) lc[b ^ 1][k] = ljj[sw(k, c + 1)];
-    }
-    x[c] *= dg[b];
-#pragma unroll
-    for (int k = c + 1; k < 16; ++k) x[k] = fma(-x[c], lc[b][k], x[k]);
-    pin_row(x);
-  }
-#pragma unroll
-  for (int c = 0; c < 16; ++c) t[sw(r, c)] = x[c];
-  if (LZ) {
-    double s = 0.0;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) s = fma(x[c], zJ[c], s);
-    lzI[r] += s;
-  }
-}
-
-// Trailing update A_IK -= L_IJ L_KJ^T of two tiles at once (two independent
-// MFMA chains); the second is computed but not stored when has1 is false.
-__device__ inline void trail_pair(double *A, int J, int I0, int K0, int I1, int K1, bool has1, int c, int q) {
-  double *t0 = A + ps::tix(I0, K0) * 256, *t1 = A + ps::tix(I1, K1) * 256;
-  const v4d a0 = ld_rm(A + ps::tix(I0, J) * 256, c, q), b0 = ld_rm(A + ps::tix(K0, J) * 256, c, q);
-  const v4d a1 = ld_rm(A + ps::tix(I1, J) * 256, c, q), b1 = ld_rm(A + ps::tix(K1, J) * 256, c, q);
-  const v4d r0 = mma(-a0, b0, ld_cm(t0, c, q));
-  const v4d r1 = mma(-a1, b1, ld_cm(t1, c, q));
-  st_cm(t0, c, q, r0);
-  if (has1) st_cm(t1, c, q, r1);
-}
-
-// (K, I) of trailing task n at step J: the pairs J < K <= I < T in order
-template <int T>
-__device__ inline void task_ki(int J, int n, int &K, int &I) {
-  K = J + 1;
-  while (n >= T - K) { n -= T - K; ++K; }
-  I = K + n;
-}
-
-// In-place X = L^-1 of the symmetric positive-definite matrix held as lower
-// tiles in A (diagonal tiles with both triangles).  All 256 threads call it.
-// flag (LDS) is set to 0 when a pivot fails; the return value is the flag;
-// flag[1] serves as a work counter.  ws: 48 + 16 T doubles of LDS scratch.  With LZ the product L z of the factor
-// with the vector z (LDS, 16 T) is accumulated into lz (LDS, zero on entry).
-//
-// Factorisation: right-looking by block columns with a lookahead of one: at
-// step J the panel is solved against L_JJ (a row per thread), then one wave
-// updates the next diagonal tile and factorises it while the other waves take
-// the rest of the trailing update and the inverse of tile J from a shared
-// counter (the factorising wave joins when done).  Inverse: X_CA = -X_CC (L_CA X_AA) for
-// neighbouring diagonal blocks A and C of s tiles, s = 1, 2, 4, ... (rows of
-// L_CA X_AA, then columns of X_CA dealt to the waves).
-template <int T, bool LZ>
-__device__ __forceinline__ bool factor_invert(double *A, int tid, int *flag, double *ws,
-                                              const double *z, double *lz) {
-  int *ctr = flag + 1;   // work counter of the trailing phases
-  const int w = tid >> 6, lane = tid & 63, c = lane & 15, q = lane >> 4;
-  const int wd = 0;   // the wave that factorises the diagonal tiles
-  // The scratch sits past 64 KB of LDS in the larger kernels, beyond a DS
-  // instruction's immediate offset: held in a register (the asm hides its
-  // constant value), its accesses take the offsets as immediates instead of
-  // forming each address anew.
-  lds_dp bc = (lds_dp)ws;
-  asm volatile("" : "+v"(bc));
-  lds_dp idg = bc + 48;   // idg: 16 per diagonal tile
-  if (w == wd) {
-    const bool ok = diag_factor<LZ>(A, bc, idg, lane, z, lz);
-    if (lane == 0 && !ok) *flag = 0;
-  }
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if (W == 1) return v;
+  const int tid = threadIdx.x;
   __syncthreads();
-#pragma unroll 1
-  for (int J = 0; J < T; ++J) {
-    {
-      const int I = J + 1 + (tid >> 4);
-      if (I < T)
-        panel_row<LZ>(A + ps::tix(I, J) * 256, A + ps::tix(J, J) * 256, idg + 16 * J, tid & 15,
-                      LZ ? z + 16 * J : nullptr, LZ ? lz + 16 * I : nullptr);
-    }
-    if (tid == 0) *ctr = 0;
-    __syncthreads();
-    if (J + 1 == T) break;
-    if (w == wd) {
-      // lookahead: tile (J+1, J+1), then its factorisation
-      double *t = A + ps::tix(J + 1, J + 1) * 256;
-      const v4d l = ld_rm(A + ps::tix(J + 1, J) * 256, c, q);
-      st_cm(t, c, q, mma(-l, l, ld_cm(t, c, q)));
-      wave_sync();
-      const bool ok = diag_factor<LZ>(t, bc, idg + 16 * (J + 1), lane, LZ ? z + 16 * (J + 1) : nullptr,
-                                      LZ ? lz + 16 * (J + 1) : nullptr);
-      if (lane == 0 && !ok) *flag = 0;
-    }
-    // the rest of the step's work, taken two items at a time from a counter:
-    // item 0 inverts tile J (its panel is done), items 1..nt are the other
-    // trailing tiles (trailing task 0 is the diagonal tile); the factorising
-    // wave joins when done
-    {
-      const int m = T - 1 - J, nt = m * (m + 1) / 2 - 1;
-      for (;;) {
-        int n0 = 0;
-        if (lane == 0) n0 = atomicAdd(ctr, 2);
-        n0 = __builtin_amdgcn_readfirstlane(n0);
-        if (n0 > nt) break;
-        if (n0 == 0) {
-          diag_inverse(A + ps::tix(J, J) * 256, idg + 16 * J, lane);
-          if (nt < 1) continue;
-          n0 = 1;
-        }
-        const bool has1 = n0 > 1 && n0 + 1 <= nt;
-        int K0, I0, K1, I1;
-        task_ki<T>(J, n0, K0, I0);
-        task_ki<T>(J, has1 ? n0 + 1 : n0, K1, I1);
-        trail_pair(A, J, I0, K0, I1, K1, has1, c, q);
-      }
-    }
-    __syncthreads();
-  }
-  // the last diagonal tile's inverse
-  if (w == 0) diag_inverse(A + ps::tix(T - 1, T - 1) * 256, idg + 16 * (T - 1), lane);
+  if ((tid & 63) == 0) red[tid >> 6] = v;
   __syncthreads();
-  // X from the diagonal inverses by doubling
+  double s = red[0];
 #pragma unroll
-  for (int sb = 1; sb < T; sb *= 2) {
-    // rows i of Y = L_CA X_AA over L_CA: block b (A = [b, b+sb), C = [b+sb, min(b+2sb, T)))
-    {
-      int item = 0;
-#pragma unroll
-      for (int b = 0; b + sb < T; b += 2 * sb) {
-#pragma unroll
-        for (int i = b + sb; i < b + 2 * sb && i < T; ++i, ++item) {
-          if ((item & 3) != w) continue;
-          v4d yv[4];
-#pragma unroll
-          for (int j = b; j < b + sb; ++j) {
-            v4d u{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int k = j; k < b + sb; ++k)
-              u = mma(ld_rm(A + ps::tix(i, k) * 256, c, q), ld_cm(A + ps::tix(k, j) * 256, c, q), u);
-            yv[j - b] = u;
-          }
-#pragma unroll
-          for (int j = b; j < b + sb; ++j) st_cm(A + ps::tix(i, j) * 256, c, q, yv[j - b]);
-        }
-      }
-    }
-    __syncthreads();
-    // columns j of X_CA = -X_CC Y over Y
-    {
-      int item = 0;
-#pragma unroll
-      for (int b = 0; b + sb < T; b += 2 * sb) {
-        const int e = (b + 2 * sb < T) ? b + 2 * sb : T;
-#pragma unroll
-        for (int j = b; j < b + sb; ++j, ++item) {
-          if ((item & 3) != w) continue;
-          v4d xv[4];
-#pragma unroll
-          for (int i = b + sb; i < e; ++i) {
-            v4d u{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int k = b + sb; k <= i; ++k)
-              u = mma(ld_rm(A + ps::tix(i, k) * 256, c, q), ld_cm(A + ps::tix(k, j) * 256, c, q), u);
-            xv[i - b - sb] = -u;
-          }
-#pragma unroll
-          for (int i = b + sb; i < e; ++i) st_cm(A + ps::tix(i, j) * 256, c, q, xv[i - b - sb]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  return *flag != 0;
-}
-
-__device__ inline double mat_at(const double *A, int r, int c) {   // lower element (r >= c)
-  return A[ps::tix(r >> 4, c >> 4) * 256 + sw(r & 15, c & 15)];
+  for (int i = 1; i < W; ++i) s += red[i];
+  return s;
 }
 
 // Block sum of one value per thread (256 threads); every thread gets the sum.
@@ -450,52 +126,41 @@ __device__ inline void block_sum3(double &a, double &b, double &c, double *red) 
   c = (red[8] + red[9]) + (red[10] + red[11]);
 }
 
-template <int T>
-constexpr size_t lds_bytes() {
-  // tiles, six vectors of 16 T, 8 reduction slots, the flag (two doubles' room)
-  // and 48 + 16 T doubles of scratch for the factorisation
-  return (size_t)(ps::ntiles(T) * 256 + 6 * 16 * T + 8 + 2 + 48 + 16 * T) * sizeof(double);
-}
-
 // ---------------------------------------------------------------------------
 // Forward per (pulsar, chain): transform, likelihood, Jacobian.
 // ---------------------------------------------------------------------------
 template <int T>
-__global__ __launch_bounds__(256, 2) void k_std_fwd(StdDev S, const double *__restrict__ x) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256, NT = ps::ntiles(T);
-  double *A = lds;
-  double *vd = A + NE, *vz = vd + pp, *vt = vz + pp, *va = vt + pp, *vdi = va + pp, *lz = vdi + pp;
-  double *red = lz + pp;
-  int *flag = reinterpret_cast<int *>(red + 8);
+__global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd(StdDev S, const double *__restrict__ x) {
+  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  using E = el::Elim<T, W>;
+  __shared__ el::Lds<T, W> L;
+  __shared__ double bv[2 * pp], tv[2 * pp], vdi[pp], red[W];   // (b, L z), (t, z), 1 / D~
+  __shared__ int flag;
   const int tid = threadIdx.x;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const double beta = S.beta ? S.beta[c] : 1.0;
   const int P = S.P;
-  const double *s0 = S.s0 + (size_t)I * pp * pp;
-  // A~ = beta S0~ + diag(1 / D~), lower tiles: thread tid holds element
-  // (tid / 16, tid % 16) of every tile; all loads are issued before any use
-  const int rr = tid >> 4, cc = tid & 15;
-  double sv[NT];
+  const size_t ci = (size_t)c * S.n_psr + I;
+  E el(tid);
+  // A~ = beta S0~ + diag(1 / D~): S0~ into the slots (rows of block C, columns
+  // of block I), every load issued before any use
+  const double *s0 = S.s0 + (size_t)I * pp * pp + el.q * pp + el.c;
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    int TI = 0;
-    while (ps::tix(TI + 1, 0) <= tt) ++TI;
-    const int TJ = tt - ps::tix(TI, 0);
-    sv[tt] = s0[(size_t)(16 * TI + rr) * pp + 16 * TJ + cc];
+  for (int s = 0; s < E::NS; ++s) {
+    const int o = el.has(s) ? 16 * (el.tile_c(s) * pp + el.tile_i(s)) : 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) el.a[s][v] = s0[o + 4 * v * pp];
   }
   int bad = 0;
-  double dr = 0.0;   // d~_r (unscaled) of this thread's row, kept for the likelihood
   // d of the data, or of the data minus the deterministic signal
-  const double *dsrc = S.has_cw ? S.dbar + ((size_t)c * S.n_psr + I) * pp : S.dvec + (size_t)I * pp;
-  for (int r = tid; r < pp; r += 256) {
-    dr = (r < P) ? dsrc[r] : 0.0;
-    vd[r] = beta * dr;
+  const double *dsrc = S.has_cw ? S.dbar + ci * pp : S.dvec + (size_t)I * pp;
+  for (int r = tid; r < pp; r += NTH) {
+    bv[2 * r] = (r < P) ? beta * dsrc[r] : 0.0;
+    bv[2 * r + 1] = 0.0;
     // with split coefficients this is the combined MAP only (z = 0)
-    vz[r] = (r < P && !S.split) ? xc[S.off_z + I * P + (P - 1 - r)] : 0.0;
-    lz[r] = 0.0;
+    tv[2 * r + 1] = (r < P && !S.split) ? xc[S.off_z + I * P + (P - 1 - r)] : 0.0;
     // a CURN variance that is not positive and finite leaves phi_CURN not
     // positive definite
     double di = 1.0;
@@ -507,96 +172,55 @@ __global__ __launch_bounds__(256, 2) void k_std_fwd(StdDev S, const double *__re
     vdi[r] = di;
   }
   bad = __syncthreads_or(bad);
-  if (tid == 0) *flag = bad ? 0 : 1;
+  if (tid == 0) flag = bad ? 0 : 1;
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    int TI = 0;
-    while (ps::tix(TI + 1, 0) <= tt) ++TI;
-    const int TJ = tt - ps::tix(TI, 0);
-    double v = beta * sv[tt];
-    if (TI == TJ && rr == cc) v += vdi[16 * TI + rr];
-    A[(tt << 8) + sw(rr, cc)] = v;
+  for (int s = 0; s < E::NS; ++s) {
+    el.a[s] *= -beta;
+    if (el.tile_i(s) == el.tile_c(s)) {
+      const double di = vdi[16 * el.tile_i(s) + el.c];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (el.q + 4 * v == el.c) el.a[s][v] -= di;
+    }
   }
   __syncthreads();
-  // X = L~^-1 and L~ z~
-  const bool ok = factor_invert<T, true>(A, tid, flag, red + 10, vz, lz);
-  // t = X beta d~ by rows: row r of X over tiles K <= r / 16 (the diagonal
-  // tiles hold zeros above), the tiles split by parity between threads r and
-  // r + 128; va and vd hold the second thread's partial sums
-  const int h = tid >> 7, r = tid & 127, R = r >> 4, r16 = r & 15;
-  const bool live = r < pp;
-  {
-    double s = 0.0;
-    if (live) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K > R) continue;
-        const double *t = A + ps::tix(R, K) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s = fma(t[sw(r16, k)], vd[16 * K + k], s);
-      }
-      if (h == 1) va[r] = s;
-    }
-    __syncthreads();
-    if (live && h == 0) vt[r] = s + va[r];
-    __syncthreads();
-  }
-  // a~ = X^T (t + z~), a_hat~ = X^T t by columns: column r over tiles K >= r / 16
-  const size_t vb = ((size_t)c * S.n_psr + I) * pp;
+  // X = L~^-1, t = X beta d~ and L~ z~
+  el.template run<1, true>(L, &flag, bv, tv, [](int) {});
+  for (int r = tid; r < pp; r += NTH) tv[2 * r + 1] += tv[2 * r];
+  __syncthreads();
+  // a_hat~ = X^T t, a~ = X^T (t + z~)
+  double *part = L.row;
+  static_assert(E::NT * 32 <= T * el::kTile, "the partial sums fit the row buffer");
+  el.xty(part, tv);
+  el::store_x(el, S.xinv + ci * (E::NT * 256));
+  __syncthreads();
   double part_d = 0.0, part_v = 0.0, part_j = 0.0;
-  {
-    double sa = 0.0, sh = 0.0;
-    if (live) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K < R) continue;
-        const double *t = A + ps::tix(K, R) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const double xv = t[sw(k, r16)], tv = vt[16 * K + k];
-          sa = fma(xv, tv + vz[16 * K + k], sa);
-          sh = fma(xv, tv, sh);
-        }
-      }
-      if (h == 1) {
-        va[r] = sa;
-        vd[r] = sh;
-      }
+  for (int r = tid; r < pp; r += NTH) {
+    const double sh = el::xty_sum<T, 2>(part, 0, r), sa = el::xty_sum<T, 2>(part, 1, r);
+    S.ahat[ci * pp + r] = sh;
+    // beta (d - S0 a) in the reversed order: A~ a~ = L~ (t + z~) = beta d~ + L~ z~,
+    // so beta S0~ a~ = beta d~ + L~ z~ - a~ / D~ and v1 = a~ / D~ - L~ z~
+    const double v1 = sa * vdi[r] - (bv[2 * r + 1] + L.lzd[r]);
+    S.v1[ci * pp + r] = v1;
+    if (r < P) {
+      S.avec[ci * pp + (P - 1 - r)] = sa;
+      part_d += sa * dsrc[r];
+      part_j += log(L.rs[r]);
     }
-    __syncthreads();
-    if (live && h == 0) {
-      sa += va[r];
-      sh += vd[r];
-      S.ahat[vb + r] = sh;
-      if (r < P) S.avec[vb + (P - 1 - r)] = sa;
-      // beta (d - S0 a) in the reversed order: A~ a~ = L~ (t + z~) = beta d~ + L~ z~,
-      // so beta S0~ a~ = beta d~ + L~ z~ - a~ / D~ and v1 = a~ / D~ - L~ z~
-      const double v1 = sa * vdi[r] - lz[r];
-      S.v1[vb + r] = v1;
-      part_d = sa * dr;
-      part_v = sa * v1;
-      part_j = (r < P) ? log(A[ps::tix(R, R) * 256 + sw(r16, r16)]) : 0.0;
-    }
+    part_v += sa * v1;
   }
-  block_sum3(part_d, part_v, part_j, red + 10);
+  part_d = wave_block_sum<W>(part_d, red);
+  part_v = wave_block_sum<W>(part_v, red);
+  part_j = wave_block_sum<W>(part_j, red);
   if (tid == 0) {
     // beta log L = beta (-dt N~^-1 dt / 2 + a.d - a.S0 a / 2 + c1), with
     // beta a.S0 a = beta a.d - a.v1
     const double *k2 = S.cconst + 2 * I;
-    const double c0 = S.has_cw ? S.cbar[(size_t)c * S.n_psr + I] : k2[0];
-    double *o = S.lik + ((size_t)c * S.n_psr + I) * 2;
+    const double c0 = S.has_cw ? S.cbar[ci] : k2[0];
+    double *o = S.lik + ci * 2;
     o[0] = beta * (k2[1] - 0.5 * c0) + 0.5 * beta * part_d + 0.5 * part_v;
     o[1] = part_j;
-    S.flag1[(size_t)c * S.n_psr + I] = ok ? 0 : ps::kFlagNotPD;
-  }
-  // X for the adjoint (16-byte copies)
-  double2 *xo = reinterpret_cast<double2 *>(S.xinv + ((size_t)c * S.n_psr + I) * NE);
-  const double2 *xa = reinterpret_cast<const double2 *>(A);
-  constexpr int N2 = NE / 2;
-#pragma unroll
-  for (int i = 0; i < (N2 + 255) / 256; ++i) {
-    const int e = tid + 256 * i;
-    if (e < N2) xo[e] = xa[e];
+    S.flag1[ci] = flag ? 0 : ps::kFlagNotPD;
   }
 }
 
@@ -604,73 +228,76 @@ __global__ __launch_bounds__(256, 2) void k_std_fwd(StdDev S, const double *__re
 // Prior per (frequency k < nf_gw, chain): phi_k = rho_k Gamma + diag kappa_.k.
 // ---------------------------------------------------------------------------
 template <int T>
-__global__ __launch_bounds__(256, 2) void k_std_prior_dense(StdDev S, const double *__restrict__ x) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256, NT = ps::ntiles(T);
-  double *A = lds;
-  double *va = A + NE, *vb = va + 2 * pp, *vu = vb + 2 * pp, *red = vu + 2 * pp;
-  int *flag = reinterpret_cast<int *>(red + 8);
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, q = lane >> 4;
+__global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) void k_std_prior_dense(StdDev S,
+                                                                                    const double *__restrict__ x) {
+  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  using E = el::Elim<T, W>;
+  __shared__ el::Lds<T, W> L;
+  __shared__ double bv[2 * pp], tv[2 * pp], vk[pp], red[W];   // a then u, y = X a (sin, cos)
+  __shared__ int flag;
+  const int tid = threadIdx.x;
   const int c = blockIdx.x / S.nf_gw, k = blockIdx.x - c * S.nf_gw;
   const int n = S.n_psr;
   const double *xc = x + (size_t)c * S.d;
-  // phi_k tiles: thread tid holds element (tid / 16, tid % 16) of every tile
-  // and of every diagonal tile's diagonal; all loads are issued before any use
-  const int rr = tid >> 4, cc = tid & 15;
-  double gv[NT], dg[T];
+  E el(tid);
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) gv[tt] = S.gam_tiles[tt * 256 + rr * 16 + cc];
+  for (int s = 0; s < E::NS; ++s) {
+    // Gamma is stored as lower tiles: the slot takes rows of block C, columns
+    // of block I, the transposed tile
+    const double *g = S.gam_tiles + (s * W + el.w < E::NT ? s * W + el.w : 0) * 256 + 16 * el.c + el.q;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) el.a[s][v] = g[4 * v];
+  }
   const double rho = ps::spec_value(S, xc, 0, 0, k);
-#pragma unroll
-  for (int TI = 0; TI < T; ++TI) {
-    const int r = 16 * TI + rr;
-    dg[TI] = (rr != cc) ? 0.0 : (r < n) ? ((k < S.nf_rn) ? ps::spec_value(S, xc, 1, r, k) : 0.0) : 1.0;
-  }
-  for (int i = tid; i < pp; i += 256) {
+  for (int i = tid; i < pp; i += NTH) {
     const double *av = S.avec + ((size_t)c * n + i) * S.pp;
-    va[i] = (i < n) ? av[2 * k] : 0.0;
-    va[pp + i] = (i < n) ? av[2 * k + 1] : 0.0;
+    vk[i] = (i < n) ? ((k < S.nf_rn) ? ps::spec_value(S, xc, 1, i, k) : 0.0) : 1.0;
+    bv[2 * i] = (i < n) ? av[2 * k] : 0.0;
+    bv[2 * i + 1] = (i < n) ? av[2 * k + 1] : 0.0;
   }
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    int TI = 0;
-    while (ps::tix(TI + 1, 0) <= tt) ++TI;
-    const int TJ = tt - ps::tix(TI, 0);
-    A[(tt << 8) + sw(rr, cc)] = (TI == TJ) ? fma(rho, gv[tt], dg[TI]) : rho * gv[tt];
-  }
-  if (tid == 0) *flag = 1;
+  if (tid == 0) flag = 1;
   __syncthreads();
-  const bool ok = factor_invert<T, false>(A, tid, flag, red + 10, nullptr, nullptr);
-  // y = X a (rows), then u = X^T y (columns), for sin and cos
-  if (tid < 2 * pp) {
-    const int i = tid % pp, h = tid / pp;
-    double s = 0.0;
-    for (int m = 0; m <= i; ++m) s = fma(mat_at(A, i, m), va[h * pp + m], s);
-    vb[h * pp + i] = s;
+#pragma unroll
+  for (int s = 0; s < E::NS; ++s) {
+    const bool dg = el.tile_i(s) == el.tile_c(s);
+    const double kv = dg ? vk[16 * el.tile_i(s) + el.c] : 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      el.a[s][v] = -fma(rho, el.a[s][v], (dg && el.q + 4 * v == el.c) ? kv : 0.0);
   }
+  // X and y = X a for sin and cos; tr(phi^-1 Gamma) = |X G|_F^2, G = chol(Gamma),
+  // row by row as X is formed: tiles (X G)_JK = sum_{M=K}^{J} X_JM G_MK
+  double part_t = 0.0;
+  el.template run<2, false>(L, &flag, bv, tv, [&](int J) {
+    for (int K = (el.w + J) % W; K <= J; K += W) {
+      v4d r{0.0, 0.0, 0.0, 0.0};
+      for (int M = K; M <= J; ++M) {
+        const v4d g = ldg_cm(S.gch_tiles + ps::tix(M, K) * 256, el.c, el.q);
+        r = ln::mfma4(el::ld_rm(M < J ? L.row + el::kTile * M : L.xjj(J), el.c, el.q), g, r);
+      }
+      part_t += (r[0] * r[0] + r[1] * r[1]) + (r[2] * r[2] + r[3] * r[3]);
+    }
+  });
+  // u = X^T y and the squared columns of X
+  double *part = L.row;
+  static_assert(E::NT * 48 <= T * el::kTile, "the partial sums fit the row buffer");
+  el.xty(part, tv);
+  el.xsq(part + E::NT * 32);
   __syncthreads();
   double part_q = 0.0, part_l = 0.0;
-  if (tid < 2 * pp) {
-    const int i = tid % pp, h = tid / pp;
-    double s = 0.0, cn = 0.0;
-    for (int m = i; m < pp; ++m) {
-      const double xv = mat_at(A, m, i);
-      s = fma(xv, vb[h * pp + m], s);
-      cn = fma(xv, xv, cn);
-    }
-    vu[h * pp + i] = s;
-    part_q = vb[h * pp + i] * vb[h * pp + i];
-    if (h == 0 && i < n) {
-      part_l = -2.0 * log(mat_at(A, i, i));
-      va[i] = cn;                                // (phi^-1)_II; a (sin) is no longer read
-    }
+  for (int i = tid; i < pp; i += NTH) {
+    bv[2 * i] = el::xty_sum<T, 2>(part, 0, i);
+    bv[2 * i + 1] = el::xty_sum<T, 2>(part, 1, i);
+    vk[i] = el::xty_sum<T, 1>(part + E::NT * 32, 0, i);   // (phi^-1)_II
+    part_q += tv[2 * i] * tv[2 * i] + tv[2 * i + 1] * tv[2 * i + 1];
+    if (i < n) part_l -= 2.0 * log(L.rs[i]);
   }
   __syncthreads();
   // Gamma u (columns of the symmetric Gamma, coalesced) for the rho term,
   // eight loads in flight at a time
   double part_g = 0.0;
-  if (tid < 2 * pp) {
-    const int i = tid % pp, h = tid / pp;
+  for (int e = tid; e < 2 * pp; e += NTH) {
+    const int i = e % pp, h = e / pp;
     if (i < n) {
       double s = 0.0;
       int m = 0;
@@ -679,39 +306,20 @@ __global__ __launch_bounds__(256, 2) void k_std_prior_dense(StdDev S, const doub
 #pragma unroll
         for (int u = 0; u < 8; ++u) g[u] = S.gamma[(size_t)(m + u) * n + i];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s = fma(g[u], vu[h * pp + m + u], s);
+        for (int u = 0; u < 8; ++u) s = fma(g[u], bv[2 * (m + u) + h], s);
       }
-      for (; m < n; ++m) s = fma(S.gamma[(size_t)m * n + i], vu[h * pp + m], s);
-      part_g = s * vu[h * pp + i];
+      for (; m < n; ++m) s = fma(S.gamma[(size_t)m * n + i], bv[2 * m + h], s);
+      part_g += s * bv[2 * i + h];
     }
   }
-  // tr(phi^-1 Gamma) = |X G|_F^2, G = chol(Gamma): tiles (X G)_IJ = sum_{K=J}^{I} X_IK G_KJ,
-  // a task's G tiles loaded together before its products
-  double part_t = 0.0;
-  {
-    int task = 0;
-#pragma unroll
-    for (int I = 0; I < T; ++I)
-#pragma unroll
-      for (int J = 0; J <= I; ++J, ++task) {
-        if ((task & 3) != w) continue;
-        v4d g[T];
-#pragma unroll
-        for (int K = J; K <= I; ++K) g[K - J] = ldg_cm(S.gch_tiles + ps::tix(K, J) * 256, c16, q);
-        v4d r{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int K = J; K <= I; ++K) r = mma(ld_rm(A + ps::tix(I, K) * 256, c16, q), g[K - J], r);
-        part_t += (r[0] * r[0] + r[1] * r[1]) + (r[2] * r[2] + r[3] * r[3]);
-      }
-  }
-  const double quad = block_sum(part_q, red);
-  const double ldet = block_sum(part_l, red);
-  const double ugu = block_sum(part_g, red);
-  const double tr = block_sum(part_t, red);
-  if (tid < n) {
-    const double u0 = vu[tid], u1 = vu[pp + tid];
-    S.dkap_e[((size_t)c * n + tid) * S.ka + k] = 0.5 * (u0 * u0 + u1 * u1) - va[tid];
-    double *v2 = S.v2 + ((size_t)c * n + tid) * S.pp;
+  const double quad = wave_block_sum<W>(part_q, red);
+  const double ldet = wave_block_sum<W>(part_l, red);
+  const double ugu = wave_block_sum<W>(part_g, red);
+  const double tr = wave_block_sum<W>(part_t, red);
+  for (int i = tid; i < n; i += NTH) {
+    const double u0 = bv[2 * i], u1 = bv[2 * i + 1];
+    S.dkap_e[((size_t)c * n + i) * S.ka + k] = 0.5 * (u0 * u0 + u1 * u1) - vk[i];
+    double *v2 = S.v2 + ((size_t)c * n + i) * S.pp;
     v2[2 * k] = -u0;
     v2[2 * k + 1] = -u1;
   }
@@ -720,7 +328,7 @@ __global__ __launch_bounds__(256, 2) void k_std_prior_dense(StdDev S, const doub
     o[0] = quad;
     o[1] = ldet;
     S.drho_e[(size_t)c * S.ka + k] = 0.5 * ugu - tr;
-    S.flag2[(size_t)c * S.ka + k] = ok ? 0 : ps::kFlagNotPD;
+    S.flag2[(size_t)c * S.ka + k] = flag ? 0 : ps::kFlagNotPD;
   }
 }
 
@@ -771,105 +379,212 @@ __global__ __launch_bounds__(256) void k_std_prior_diag(StdDev S, const double *
 // ---------------------------------------------------------------------------
 // Adjoint per (pulsar, chain): dlogp/dz and dlogp/dD.
 // ---------------------------------------------------------------------------
+
+// Lane l ^ (2 M - 1) of a 16-lane row, M = 8, 4, 2, 1: the mirror of the row,
+// of its halves, of its quads, of its pairs (DPP).
+template <int M>
+__device__ inline double mirror_d(double v) {
+  constexpr int ctrl = M == 8 ? 0x140 : M == 4 ? 0x141 : M == 2 ? 0x1B : 0xB1;
+  const long long b = __double_as_longlong(v);
+  return ln::join_d(__builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xF, 0xF, false),
+                    __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xF, 0xF, false));
+}
+
+// Sums of N = 16, 8 or 4 values over the 16 lanes of a row: lane c ends with
+// the sum of value c N / 16 (halves of the values go to the two halves of the
+// lanes until one is left).
+template <int N>
+__device__ __forceinline__ double row_sums(double (&v)[N], int c) {
+  if (N >= 2) {
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+      const bool up = c & 8;
+      v[i] = (up ? v[i + N / 2] : v[i]) + mirror_d<8>(up ? v[i] : v[i + N / 2]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) {
+    const bool up = c & 4;
+    v[i] = (up ? v[i + N / 4] : v[i]) + mirror_d<4>(up ? v[i] : v[i + N / 4]);
+  }
+  if (N >= 8) {
+#pragma unroll
+    for (int i = 0; i < N / 8; ++i) {
+      const bool up = c & 2;
+      v[i] = (up ? v[i + N / 8] : v[i]) + mirror_d<2>(up ? v[i] : v[i + N / 8]);
+    }
+  } else {
+    v[0] += mirror_d<2>(v[0]);
+  }
+  if (N >= 16) {
+    const bool up = c & 1;
+    v[0] = (up ? v[1] : v[0]) + mirror_d<1>(up ? v[0] : v[1]);
+  } else {
+    v[0] += mirror_d<1>(v[0]);
+  }
+  return v[0];
+}
+
+// The sums of a column over its rows a, top to bottom, that the adjoint needs:
+// sv = sum X_ar w_a, ss = sum X_ar^2, suf = sum X_ar z_a and
+// tt = sum_a X_ar w_a (sum_{b>a} X_br z_b + X_ar z_a / 2).
+struct ColSum {
+  double sv, ss, suf, tt;
+  __device__ inline void below(const ColSum &o) {   // this column's rows, then those of o
+    tt += o.tt + sv * o.suf;
+    sv += o.sv;
+    ss += o.ss;
+    suf += o.suf;
+  }
+};
+
+// The adjoint reads all of X once (316 MB a launch at 67 pulsars x 64 chains,
+// T = 8), which bounds it: 3.3 TB/s and 95 us there; through LDS, two problems a
+// compute unit and a thread per half row and half column, it took 136.
+//
+// X of one problem (block columns of 16, see el::store_x) in registers: wave w
+// of (T + 1) / 2 takes the block columns w and T - 1 - w, 4 (T + 1) values a lane
+// in all (half of that for the middle one of an odd T), so that the waves are
+// even.  Lane (c, q) holds a quarter q of the rows of column c, consecutive
+// ones: the sums down a column run in one lane and only their four parts are
+// put together across lanes.  X is read once, 128 bytes a row of 16 lanes.
 template <int T>
-__global__ __launch_bounds__(256) void k_std_bwd(StdDev S, const double *__restrict__ x,
-                                                  double *__restrict__ grad) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256;
-  double *A = lds;
-  double *vv = A + NE, *vz = vv + pp, *vw = vz + pp, *vh = vw + pp, *gd = vh + pp, *tmp = gd + pp;
+struct AdjX {
+  static constexpr int W = (T + 1) / 2, NI = 4 * (T + 1), pp = 16 * T;
+  int w, c, q, C2, n1, n2;
+  double x[NI];
+
+  __device__ __forceinline__ AdjX(const double *__restrict__ xi, int tid)
+      : w(W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6)), c(tid & 15), q((tid & 63) >> 4), C2(T - 1 - w),
+        n1(4 * (T - w)), n2(C2 != w ? 4 * (w + 1) : 0) {
+    const double *p1 = xi + (el::cix<T>(w) + q * n1) * 16 + c;
+    const double *p2 = xi + (el::cix<T>(C2) + q * n2 - n1) * 16 + c;
+#pragma unroll
+    for (int k = 0; k < NI; ++k) x[k] = k < n1 ? p1[k * 16] : k < n1 + n2 ? p2[k * 16] : 0.0;
+  }
+  __device__ inline int row_of(int k) const { return k < n1 ? 16 * w + q * n1 + k : 16 * C2 + q * n2 + k - n1; }
+
+  // This wave's part of X v by rows to wp[T][pp] (LDS): row r over block column
+  // C in wp[C][r]; after a barrier row_total adds a row's block columns in order.
+  template <int N>
+  __device__ __forceinline__ void rows_part(int k0, const double v1, const double v2, double *wp) {
+    double p[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = x[k0 + i] * (k0 + i < n1 ? v1 : v2);
+    const double s = row_sums<N>(p, c);
+    const int k = k0 + c * N / 16;
+    if (c % (16 / N) == 0 && k < n1 + n2) wp[(k < n1 ? w : C2) * pp + row_of(k)] = s;
+  }
+  __device__ __forceinline__ void rows(const double *v, double *wp) {
+    const double v1 = v[16 * w + c], v2 = v[16 * C2 + c];
+    constexpr int n16 = NI / 16;
+#pragma unroll
+    for (int g = 0; g < n16; ++g) rows_part<16>(16 * g, v1, v2, wp);
+    if constexpr (NI % 16 >= 8) rows_part<8>(16 * n16, v1, v2, wp);
+    if constexpr (NI % 8 >= 4) rows_part<4>(NI - 4, v1, v2, wp);
+  }
+  static __device__ inline double row_total(const double *wp, int r) {
+    double s = 0.0;
+    for (int C = 0; C <= (r >> 4); ++C) s += wp[C * pp + r];
+    return s;
+  }
+
+  // Column sums of the wave's block columns: sink(column, sums) in the lanes
+  // of row 0, wz[r] = (w_r, z_r) (LDS).
+  template <class Sink>
+  __device__ __forceinline__ void columns(const double2 *wz, Sink sink) {
+    ColSum s{0.0, 0.0, 0.0, 0.0}, s2{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = NI - 1; k >= 0; --k) {
+      if (k >= n1 + n2) continue;
+      if (k == n1 - 1) {   // the second block column is done
+        s2 = s;
+        s = ColSum{0.0, 0.0, 0.0, 0.0};
+      }
+      const double2 a = wz[row_of(k)];
+      const double xv = x[k], xw = xv * a.x;
+      s.tt = fma(xw, fma(0.5 * xv, a.y, s.suf), s.tt);
+      s.sv += xw;
+      s.ss = fma(xv, xv, s.ss);
+      s.suf = fma(xv, a.y, s.suf);
+    }
+    finish(s, w, sink);
+    if (n2 > 0) finish(s2, C2, sink);
+  }
+  template <class Sink>
+  __device__ __forceinline__ void finish(ColSum s, int C, Sink sink) {
+    // quarters q, q ^ 1 and then the halves, the upper rows first
+#pragma unroll
+    for (int m = 1; m <= 2; m *= 2) {
+      const bool lower = q & m;
+      const ColSum o = m == 1 ? ColSum{ln::xor16_d(s.sv, q), ln::xor16_d(s.ss, q), ln::xor16_d(s.suf, q),
+                                       ln::xor16_d(s.tt, q)}
+                              : ColSum{ln::xor32_d(s.sv, q), ln::xor32_d(s.ss, q), ln::xor32_d(s.suf, q),
+                                       ln::xor32_d(s.tt, q)};
+      ColSum u = lower ? o : s;
+      u.below(lower ? s : o);
+      s = u;
+    }
+    if (q == 0) sink(16 * C + c, s);
+  }
+};
+
+template <int T>
+__global__ __launch_bounds__(64 * AdjX<T>::W, 4) void k_std_bwd(StdDev S, const double *__restrict__ x,
+                                                             double *__restrict__ grad) {
+  constexpr int W = AdjX<T>::W, pp = 16 * T, NTH = 64 * W;
+  __shared__ double wp[T * pp], vv[pp], gd[pp], sg[pp];
+  __shared__ double2 wz[pp];
   const int tid = threadIdx.x;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const int P = S.P;
-  const size_t vb = ((size_t)c * S.n_psr + I) * pp;
-  {
-    const double2 *xi = reinterpret_cast<const double2 *>(S.xinv + ((size_t)c * S.n_psr + I) * NE);
-    double2 *xa = reinterpret_cast<double2 *>(A);
-    constexpr int N2 = NE / 2;
-#pragma unroll
-    for (int i = 0; i < (N2 + 255) / 256; ++i) {
-      const int e = tid + 256 * i;
-      if (e < N2) xa[e] = xi[e];
-    }
-  }
-  for (int r = tid; r < pp; r += 256) {
+  const size_t ci = (size_t)c * S.n_psr + I, vb = ci * pp;
+  AdjX<T> X(S.xinv + ci * (ps::ntiles(T) * 256), tid);
+  static_assert(NTH >= pp, "a thread per row");
+  const int r = tid;
+  double zr = 0.0, ah = 0.0, Dv = 1.0;
+  if (r < pp) {
     vv[r] = (r < P) ? S.v1[vb + r] + S.v2[vb + (P - 1 - r)] : 0.0;
-    vz[r] = (r < P) ? xc[S.off_z + I * P + (P - 1 - r)] : 0.0;
-    vh[r] = S.ahat[vb + r];
+    if (r < P) {
+      zr = xc[S.off_z + I * P + (P - 1 - r)];
+      ah = S.ahat[vb + r];
+      Dv = ps::curn_var(S, xc, I, P - 1 - r);
+    }
   }
   __syncthreads();
-  const int h = tid >> 7, r = tid & 127, R = r >> 4, r16 = r & 15;
-  // w~ = X v~ (dlogp/dz~) by rows, the tiles split by parity between threads r
-  // and r + 128
-  {
-    double s = 0.0;
-    if (r < pp) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K > R) continue;
-        const double *t = A + ps::tix(R, K) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s = fma(t[sw(r16, k)], vv[16 * K + k], s);
-      }
-      if (h == 1) tmp[r] = s;
-    }
-    __syncthreads();
-    if (r < pp && h == 0) {
-      s += tmp[r];
-      vw[r] = s;
-      if (r < P) grad[(size_t)c * S.d + S.off_z + I * P + (P - 1 - r)] = s;
-    }
-    __syncthreads();
+  // w~ = X v~ (dlogp/dz~)
+  X.rows(vv, wp);
+  __syncthreads();
+  if (r < pp) {
+    const double s = AdjX<T>::row_total(wp, r);
+    wz[r] = double2{s, zr};
+    if (r < P) grad[(size_t)c * S.d + S.off_z + I * P + (P - 1 - r)] = s;
   }
-  // per column r, over rows a >= r from the bottom: (Sigma v)~_r = sum_a X_ar w~_a,
-  // Sigma~_rr = sum_a X_ar^2 and T_r = sum_a X_ar w~_a (sum_{b>a} X_br z~_b + X_ar z~_a / 2),
-  // dlogp/dD~_r = (a_hat~_r (Sigma v)~_r + T_r + Sigma~_rr / 2) / D~_r^2.
-  // Thread r + 128 takes the lower tiles K >= M, thread r the tiles R..M-1; the
-  // upper part's suffix sums miss the lower part's s = sum_b X_br z~_b, which
-  // adds s times the upper part's sum_a X_ar w~_a.  The lower part hands over
-  // s and its own a_hat (Sigma v) + T + Sigma / 2.
-  double sv = 0.0, ss = 0.0, tt = 0.0, suf = 0.0;
+  __syncthreads();
+  // per column r: (Sigma v)~_r, Sigma~_rr and T_r;
+  // dlogp/dD~_r = (a_hat~_r (Sigma v)~_r + T_r + Sigma~_rr / 2) / D~_r^2
+  X.columns(wz, [&](int col, const ColSum &s) {
+    sg[col] = s.sv;
+    gd[col] = s.tt + 0.5 * s.ss;
+  });
+  __syncthreads();
   if (r < P) {
-    const int M = R + (T - R + 1) / 2;
-#pragma unroll
-    for (int K = T - 1; K >= 0; --K) {
-      if (K < R || (h == 1) != (K >= M)) continue;
-      const double *t = A + ps::tix(K, R) * 256;
-#pragma unroll
-      for (int k = 15; k >= 0; --k) {
-        const double xv = t[sw(k, r16)], wv = vw[16 * K + k], zv = vz[16 * K + k];
-        sv = fma(xv, wv, sv);
-        ss = fma(xv, xv, ss);
-        tt = fma(xv * wv, fma(0.5 * xv, zv, suf), tt);
-        suf = fma(xv, zv, suf);
-      }
-    }
-    if (h == 1) {
-      tmp[r] = suf;
-      tmp[pp + r] = fma(vh[r], sv, tt + 0.5 * ss);
-      vv[r] = sv;   // v~ is no longer read
-    }
-  }
-  __syncthreads();
-  if (r < P && h == 0) {
-    const double Dv = ps::curn_var(S, xc, I, P - 1 - r);
-    gd[r] = (fma(sv, vh[r] + tmp[r], tt + 0.5 * ss) + tmp[pp + r]) / (Dv * Dv);
+    gd[r] = fma(ah, sg[r], gd[r]) / (Dv * Dv);
     if (S.has_cw) {
       // dlog p / d d_bar (original order): beta a (likelihood) + beta Sigma v (a_hat)
       const double beta = S.beta ? S.beta[c] : 1.0;
       const int j = P - 1 - r;
-      S.gdbar[((size_t)c * S.n_psr + I) * P + j] = beta * (S.avec[vb + j] + (sv + vv[r]));
+      S.gdbar[ci * P + j] = beta * (S.avec[vb + j] + sg[r]);
     }
   }
   __syncthreads();
-  if (tid < S.ka) {
-    const int r0 = P - 1 - 2 * tid, r1 = r0 - 1;
-    S.dD_rn[((size_t)c * S.n_psr + I) * S.ka + tid] = gd[r0] + gd[r1];
-  } else if (tid >= 64 && tid - 64 < S.kdm) {
-    const int k = tid - 64, r0 = P - 1 - (2 * S.ka + 2 * k), r1 = r0 - 1;
-    S.dD_dm[((size_t)c * S.n_psr + I) * S.kdm + k] = gd[r0] + gd[r1];
+  if (tid < S.ka + S.kdm) {
+    const int r0 = P - 1 - 2 * tid, r1 = r0 - 1;   // the DM block follows the red/common one
+    const double g = gd[r0] + gd[r1];
+    if (tid < S.ka) S.dD_rn[ci * S.ka + tid] = g;
+    else S.dD_dm[ci * S.kdm + (tid - S.ka)] = g;
   }
 }
 
@@ -1460,31 +1175,32 @@ __global__ __launch_bounds__(kFinT) void k_std_finalize(StdDev S, const double *
 // Set b of pulsar I, chain c: A~ = beta S0_b~ + diag(1 / v~) factorised and
 // inverted as the CURN precision is; L_b z_b = X^T z~ and ln det L_b.
 template <int T>
-__global__ __launch_bounds__(256, 2) void k_split_fac(StdDev S, const double *__restrict__ x, int b) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256, NT = ps::ntiles(T);
-  double *A = lds;
-  double *vz = A + NE, *va = vz + pp, *red = va + pp;
-  int *flag = reinterpret_cast<int *>(red + 8);
+__global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_split_fac(StdDev S, const double *__restrict__ x,
+                                                                              int b) {
+  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  using E = el::Elim<T, W>;
+  __shared__ el::Lds<T, W> L;
+  __shared__ double zv[2 * pp], va[pp], red[W];
+  __shared__ int flag;
   const int tid = threadIdx.x;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const double beta = S.beta ? S.beta[c] : 1.0;
   const int PB = b ? S.PR : S.PG;
-  const double *s0 = (b ? S.s0r : S.s0g) + (size_t)I * pp * pp;
-  const int rr = tid >> 4, cc = tid & 15;
-  double sv[NT];
+  const size_t ci = (size_t)c * S.n_psr + I;
+  E el(tid);
+  const double *s0 = (b ? S.s0r : S.s0g) + (size_t)I * pp * pp + el.q * pp + el.c;
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    int TI = 0;
-    while (ps::tix(TI + 1, 0) <= tt) ++TI;
-    const int TJ = tt - ps::tix(TI, 0);
-    sv[tt] = s0[(size_t)(16 * TI + rr) * pp + 16 * TJ + cc];
+  for (int s = 0; s < E::NS; ++s) {
+    const int o = el.has(s) ? 16 * (el.tile_c(s) * pp + el.tile_i(s)) : 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) el.a[s][v] = s0[o + 4 * v * pp];
   }
   int bad = 0;
-  for (int r = tid; r < pp; r += 256) {
-    vz[r] = (r < PB) ? xc[S.off_z + I * S.pz + (b ? S.PG : 0) + (PB - 1 - r)] : 0.0;
+  for (int r = tid; r < pp; r += NTH) {
+    zv[2 * r] = (r < PB) ? xc[S.off_z + I * S.pz + (b ? S.PG : 0) + (PB - 1 - r)] : 0.0;
+    zv[2 * r + 1] = 0.0;
     double di = 1.0;
     if (r < PB) {
       const double v = ps::split_var(S, xc, I, b, PB - 1 - r);
@@ -1494,53 +1210,32 @@ __global__ __launch_bounds__(256, 2) void k_split_fac(StdDev S, const double *__
     va[r] = di;
   }
   bad = __syncthreads_or(bad);
-  if (tid == 0) *flag = bad ? 0 : 1;
+  if (tid == 0) flag = bad ? 0 : 1;
 #pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    int TI = 0;
-    while (ps::tix(TI + 1, 0) <= tt) ++TI;
-    const int TJ = tt - ps::tix(TI, 0);
-    double v = beta * sv[tt];
-    if (TI == TJ && rr == cc) v += va[16 * TI + rr];
-    A[(tt << 8) + sw(rr, cc)] = v;
+  for (int s = 0; s < E::NS; ++s) {
+    el.a[s] *= -beta;
+    if (el.tile_i(s) == el.tile_c(s)) {
+      const double di = va[16 * el.tile_i(s) + el.c];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (el.q + 4 * v == el.c) el.a[s][v] -= di;
+    }
   }
   __syncthreads();
-  const bool ok = factor_invert<T, false>(A, tid, flag, red + 10, nullptr, nullptr);
-  // X^T z~ by columns (column r over tiles K >= r / 16), the tiles split by
-  // parity between threads r and r + 128
-  const int h = tid >> 7, r = tid & 127, R = r >> 4, r16 = r & 15;
-  const size_t ci = (size_t)c * S.n_psr + I;
+  el.template run<0, false>(L, &flag, nullptr, nullptr, [](int) {});
+  double *part = L.row;
+  el.xty(part, zv);
+  el::store_x(el, (b ? S.xr : S.xg) + ci * (E::NT * 256));
+  __syncthreads();
   double part_j = 0.0;
-  {
-    double sa = 0.0;
-    if (r < pp) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K < R) continue;
-        const double *t = A + ps::tix(K, R) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) sa = fma(t[sw(k, r16)], vz[16 * K + k], sa);
-      }
-      if (h == 1) va[r] = sa;
-    }
-    __syncthreads();
-    if (r < PB && h == 0) {
-      (b ? S.lzr : S.lzg)[ci * pp + (PB - 1 - r)] = sa + va[r];
-      part_j = log(A[ps::tix(R, R) * 256 + sw(r16, r16)]);
-    }
+  for (int r = tid; r < PB; r += NTH) {
+    (b ? S.lzr : S.lzg)[ci * pp + (PB - 1 - r)] = el::xty_sum<T, 2>(part, 0, r);
+    part_j += log(L.rs[r]);
   }
-  part_j = block_sum(part_j, red);
+  part_j = wave_block_sum<W>(part_j, red);
   if (tid == 0) {
     S.jac_s[ci * 2 + b] = part_j;
-    S.flag_s[ci * 2 + b] = ok ? 0 : ps::kFlagNotPD;
-  }
-  double2 *xo = reinterpret_cast<double2 *>((b ? S.xr : S.xg) + ci * NE);
-  const double2 *xa = reinterpret_cast<const double2 *>(A);
-  constexpr int N2 = NE / 2;
-#pragma unroll
-  for (int i = 0; i < (N2 + 255) / 256; ++i) {
-    const int e = tid + 256 * i;
-    if (e < N2) xo[e] = xa[e];
+    S.flag_s[ci * 2 + b] = flag ? 0 : ps::kFlagNotPD;
   }
 }
 
@@ -1636,79 +1331,46 @@ __global__ __launch_bounds__(256) void k_split_prior_g(StdDev S, const double *_
 // with T_r and Sigma~_rr as in k_std_bwd (no MAP term: the sets' MAP comes
 // from the combined problem).
 template <int T>
-__global__ __launch_bounds__(256) void k_split_bwd(StdDev S, const double *__restrict__ x,
-                                                    double *__restrict__ grad, int b) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256;
-  double *A = lds;
-  double *vv = A + NE, *vz = vv + pp, *vw = vz + pp, *tmp = vw + pp;
+__global__ __launch_bounds__(64 * AdjX<T>::W, 4) void k_split_bwd(StdDev S, const double *__restrict__ x,
+                                                               double *__restrict__ grad, int b) {
+  constexpr int pp = 16 * T;
+  __shared__ double wp[T * pp], vv[pp], gd[pp];
+  __shared__ double2 wz[pp];
   const int tid = threadIdx.x;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const int PB = b ? S.PR : S.PG, P = S.P;
   const size_t ci = (size_t)c * S.n_psr + I;
-  {
-    const double2 *xi = reinterpret_cast<const double2 *>((b ? S.xr : S.xg) + ci * NE);
-    double2 *xa = reinterpret_cast<double2 *>(A);
-    constexpr int N2 = NE / 2;
-#pragma unroll
-    for (int i = 0; i < (N2 + 255) / 256; ++i) {
-      const int e = tid + 256 * i;
-      if (e < N2) xa[e] = xi[e];
-    }
-  }
+  AdjX<T> X((b ? S.xr : S.xg) + ci * (ps::ntiles(T) * 256), tid);
   const int zo = S.off_z + I * S.pz + (b ? S.PG : 0);
-  for (int r = tid; r < pp; r += 256) {
-    double g = 0.0, z = 0.0;
+  const int r = tid;
+  double zr = 0.0;
+  if (r < pp) {
+    double g = 0.0;
     if (r < PB) {
       const int j = PB - 1 - r, jc = ps::split_row(S, b, j);
       g = S.v1[ci * S.pp + (P - 1 - jc)] + (b ? S.v2r[ci * pp + j] : S.v2[ci * S.pp + j]);
       (b ? S.gar : S.gag)[ci * pp + j] = g;
-      z = xc[zo + j];
+      zr = xc[zo + j];
     }
     vv[r] = g;
-    vz[r] = z;
   }
   __syncthreads();
-  const int h = tid >> 7, r = tid & 127, R = r >> 4, r16 = r & 15;
-  {
-    double s = 0.0;
-    if (r < pp) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K > R) continue;
-        const double *t = A + ps::tix(R, K) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s = fma(t[sw(r16, k)], vv[16 * K + k], s);
-      }
-      if (h == 1) tmp[r] = s;
-    }
-    __syncthreads();
-    if (r < pp && h == 0) {
-      s += tmp[r];
-      vw[r] = s;
-      if (r < PB) grad[(size_t)c * S.d + zo + (PB - 1 - r)] = s;
-    }
-    __syncthreads();
+  X.rows(vv, wp);
+  __syncthreads();
+  if (r < pp) {
+    const double s = AdjX<T>::row_total(wp, r);
+    wz[r] = double2{s, zr};
+    if (r < PB) grad[(size_t)c * S.d + zo + (PB - 1 - r)] = s;
   }
-  // column r from the bottom: Sigma~_rr = sum_a X_ar^2 and
-  // T_r = sum_a X_ar w~_a (sum_{b>a} X_br z~_b + X_ar z~_a / 2)
-  if (tid < PB) {
-    double ss = 0.0, tt = 0.0, suf = 0.0;
-    for (int K = T - 1; K >= R; --K) {
-      const double *t = A + ps::tix(K, R) * 256;
-#pragma unroll
-      for (int k = 15; k >= 0; --k) {
-        const double xv = t[sw(k, r16)], wv = vw[16 * K + k], zv = vz[16 * K + k];
-        ss = fma(xv, xv, ss);
-        tt = fma(xv * wv, fma(0.5 * xv, zv, suf), tt);
-        suf = fma(xv, zv, suf);
-      }
-    }
+  __syncthreads();
+  X.columns(wz, [&](int col, const ColSum &s) { gd[col] = s.tt + 0.5 * s.ss; });
+  __syncthreads();
+  if (r < PB) {
     const int j = PB - 1 - r;
     const double v = ps::split_var(S, xc, I, b, j);
-    (b ? S.ddr : S.ddg)[ci * pp + j] = (tt + 0.5 * ss) / (v * v);
+    (b ? S.ddr : S.ddg)[ci * pp + j] = gd[r] / (v * v);
   }
 }
 
@@ -1722,33 +1384,25 @@ __global__ __launch_bounds__(256) void k_split_bwd(StdDev S, const double *__res
 // pulsar's part of dlog p / drho_k (drho_p) and dlog p / dkappa (dD_rn, dD_dm).
 // With a CW, dlog p / d d_bar = beta (a + Sigma g).
 template <int T>
-__global__ __launch_bounds__(256) void k_split_bwd_c(StdDev S, const double *__restrict__ x) {
-  extern __shared__ double lds[];
-  constexpr int pp = 16 * T, NE = ps::ntiles(T) * 256;
-  double *A = lds;
-  double *vv = A + NE, *vw = vv + pp, *tmp = vw + pp, *prt = tmp + pp, *pkt = prt + pp;
+__global__ __launch_bounds__(64 * AdjX<T>::W, T == 8 ? 3 : 4) void k_split_bwd_c(StdDev S, const double *__restrict__ x) {
+  constexpr int pp = 16 * T;
+  __shared__ double wp[T * pp], vv[pp], sg[pp], prt[pp], pkt[pp];
+  __shared__ double2 wz[pp];
   const int tid = threadIdx.x;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const int P = S.P;
   const size_t ci = (size_t)c * S.n_psr + I, vb = ci * pp;
-  {
-    const double2 *xi = reinterpret_cast<const double2 *>(S.xinv + ci * NE);
-    double2 *xa = reinterpret_cast<double2 *>(A);
-    constexpr int N2 = NE / 2;
-#pragma unroll
-    for (int i = 0; i < (N2 + 255) / 256; ++i) {
-      const int e = tid + 256 * i;
-      if (e < N2) xa[e] = xi[e];
-    }
-  }
-  // this thread's row j (original order), kept for the chain rule
-  double rho = 0.0, phi = 0.0, gG = 0.0, gR = 0.0, D = 1.0;
+  AdjX<T> X(S.xinv + ci * (ps::ntiles(T) * 256), tid);
+  // this thread's row r of X (row j = P - 1 - r of the original order), kept for
+  // the chain rule
+  const int r = tid, j = P - 1 - r;
+  double rho = 0.0, phi = 0.0, gG = 0.0, gR = 0.0, D = 1.0, ah = 0.0;
   int jr = -1;
-  if (tid < P) {
-    const int j = tid;
+  if (r < P) {
     D = ps::curn_var(S, xc, I, j);
+    ah = S.ahat[vb + r];
     if (j < S.PG) {
       rho = ps::spec_value(S, xc, 0, I, j >> 1);
       gG = S.gag[ci * S.ppg + j];
@@ -1759,108 +1413,50 @@ __global__ __launch_bounds__(256) void k_split_bwd_c(StdDev S, const double *__r
       gR = S.gar[ci * S.ppr + jr];
     }
   }
-  for (int r = tid; r < pp; r += 256) vv[r] = 0.0;
+  if (r < pp) vv[r] = r < P ? (rho * gG + phi * gR) / D : 0.0;
   __syncthreads();
-  if (tid < P) vv[P - 1 - tid] = (rho * gG + phi * gR) / D;
+  X.rows(vv, wp);
   __syncthreads();
-  const int h = tid >> 7, r = tid & 127, R = r >> 4, r16 = r & 15;
-  {
-    double s = 0.0;
-    if (r < pp) {
-#pragma unroll
-      for (int K = 0; K < T; ++K) {
-        if ((K & 1) != h || K > R) continue;
-        const double *t = A + ps::tix(R, K) * 256;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s = fma(t[sw(r16, k)], vv[16 * K + k], s);
-      }
-      if (h == 1) tmp[r] = s;
-    }
-    __syncthreads();
-    if (r < pp && h == 0) vw[r] = s + tmp[r];
-    __syncthreads();
-  }
-  // (Sigma g)~_r = sum_{a >= r} X_ar w~_a, one thread per column
-  if (tid < P) {
-    const int rc = P - 1 - tid, Rc = rc >> 4, rc16 = rc & 15;
-    double sg = 0.0;
-    for (int K = Rc; K < T; ++K) {
-      const double *t = A + ps::tix(K, Rc) * 256;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) sg = fma(t[sw(k, rc16)], vw[16 * K + k], sg);
-    }
-    const int j = tid;
-    const double ah = S.ahat[vb + rc];
+  if (r < pp) wz[r] = double2{AdjX<T>::row_total(wp, r), 0.0};
+  __syncthreads();
+  // (Sigma g)~_r = sum_{a >= r} X_ar w~_a
+  X.columns(wz, [&](int col, const ColSum &s) { sg[col] = s.sv; });
+  __syncthreads();
+  if (r < P) {
     const double q = ah / (D * D);
-    const double dD = sg * q;
+    const double dD = sg[r] * q;
     prt[j] = (j < S.PG) ? dD + phi * q * (gG - gR) + S.ddg[ci * S.ppg + j] : 0.0;
     pkt[j] = (jr >= 0) ? dD + rho * q * (gR - gG) + S.ddr[ci * S.ppr + jr] : 0.0;
     if (S.has_cw) {
       const double beta = S.beta ? S.beta[c] : 1.0;
-      S.gdbar[ci * P + j] = beta * (S.avec[vb + j] + sg);
+      S.gdbar[ci * P + j] = beta * (S.avec[vb + j] + sg[r]);
     }
   }
   __syncthreads();
-  if (tid < S.nf_gw) {
-    S.drho_p[ci * S.ka + tid] = prt[2 * tid] + prt[2 * tid + 1];
-  } else if (tid >= 64 && tid - 64 < S.nf_rn) {
-    const int k = tid - 64;
-    S.dD_rn[ci * S.ka + k] = pkt[2 * k] + pkt[2 * k + 1];
-  } else if (tid >= 128 && tid - 128 < S.kdm) {
-    const int k = tid - 128;
+  for (int k = tid; k < S.nf_gw; k += blockDim.x) S.drho_p[ci * S.ka + k] = prt[2 * k] + prt[2 * k + 1];
+  for (int k = tid; k < S.nf_rn; k += blockDim.x) S.dD_rn[ci * S.ka + k] = pkt[2 * k] + pkt[2 * k + 1];
+  for (int k = tid; k < S.kdm; k += blockDim.x)
     S.dD_dm[ci * S.kdm + k] = pkt[2 * S.ka + 2 * k] + pkt[2 * S.ka + 2 * k + 1];
-  }
-}
-
-template <int T>
-hipError_t set_attr_t() {
-  hipError_t e = hipFuncSetAttribute((const void *)k_std_fwd<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds_bytes<T>());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_std_prior_dense<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds_bytes<T>());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_split_fac<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds_bytes<T>());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_split_bwd<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds_bytes<T>());
-  if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute((const void *)k_split_bwd_c<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds_bytes<T>());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void *)k_std_bwd<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)lds_bytes<T>());
 }
 
 }  // namespace
 
 namespace psk {
 
-hipError_t init_attributes() {
-  hipError_t e;
-  if ((e = set_attr_t<1>()) != hipSuccess) return e;
-  if ((e = set_attr_t<2>()) != hipSuccess) return e;
-  if ((e = set_attr_t<3>()) != hipSuccess) return e;
-  if ((e = set_attr_t<4>()) != hipSuccess) return e;
-  if ((e = set_attr_t<5>()) != hipSuccess) return e;
-  if ((e = set_attr_t<6>()) != hipSuccess) return e;
-  if ((e = set_attr_t<7>()) != hipSuccess) return e;
-  return set_attr_t<8>();
-}
-
-#define PS_DISPATCH(TT, KERNEL, GRID, ...)                                                          \
-  switch (TT) {                                                                                     \
-    case 1: hipLaunchKernelGGL(KERNEL<1>, dim3(GRID), dim3(256), lds_bytes<1>(), s, __VA_ARGS__); break; \
-    case 2: hipLaunchKernelGGL(KERNEL<2>, dim3(GRID), dim3(256), lds_bytes<2>(), s, __VA_ARGS__); break; \
-    case 3: hipLaunchKernelGGL(KERNEL<3>, dim3(GRID), dim3(256), lds_bytes<3>(), s, __VA_ARGS__); break; \
-    case 4: hipLaunchKernelGGL(KERNEL<4>, dim3(GRID), dim3(256), lds_bytes<4>(), s, __VA_ARGS__); break; \
-    case 5: hipLaunchKernelGGL(KERNEL<5>, dim3(GRID), dim3(256), lds_bytes<5>(), s, __VA_ARGS__); break; \
-    case 6: hipLaunchKernelGGL(KERNEL<6>, dim3(GRID), dim3(256), lds_bytes<6>(), s, __VA_ARGS__); break; \
-    case 7: hipLaunchKernelGGL(KERNEL<7>, dim3(GRID), dim3(256), lds_bytes<7>(), s, __VA_ARGS__); break; \
-    case 8: hipLaunchKernelGGL(KERNEL<8>, dim3(GRID), dim3(256), lds_bytes<8>(), s, __VA_ARGS__); break; \
-    default: return hipErrorInvalidValue;                                                           \
+#define PS_DISPATCH(TT, KERNEL, WAVES, GRID, ...)                                            \
+  switch (TT) {                                                                              \
+    case 1: hipLaunchKernelGGL(KERNEL<1>, dim3(GRID), dim3(64 * WAVES(1)), 0, s, __VA_ARGS__); break; \
+    case 2: hipLaunchKernelGGL(KERNEL<2>, dim3(GRID), dim3(64 * WAVES(2)), 0, s, __VA_ARGS__); break; \
+    case 3: hipLaunchKernelGGL(KERNEL<3>, dim3(GRID), dim3(64 * WAVES(3)), 0, s, __VA_ARGS__); break; \
+    case 4: hipLaunchKernelGGL(KERNEL<4>, dim3(GRID), dim3(64 * WAVES(4)), 0, s, __VA_ARGS__); break; \
+    case 5: hipLaunchKernelGGL(KERNEL<5>, dim3(GRID), dim3(64 * WAVES(5)), 0, s, __VA_ARGS__); break; \
+    case 6: hipLaunchKernelGGL(KERNEL<6>, dim3(GRID), dim3(64 * WAVES(6)), 0, s, __VA_ARGS__); break; \
+    case 7: hipLaunchKernelGGL(KERNEL<7>, dim3(GRID), dim3(64 * WAVES(7)), 0, s, __VA_ARGS__); break; \
+    case 8: hipLaunchKernelGGL(KERNEL<8>, dim3(GRID), dim3(64 * WAVES(8)), 0, s, __VA_ARGS__); break; \
+    default: return hipErrorInvalidValue;                                                    \
   }
+#define ELIM_WAVES(T) elim_waves<T>()
+#define ADJ_WAVES(T) AdjX<T>::W
 
 hipError_t launch_std_cw_fwd(const StdDev &S, const double *x, hipStream_t s) {
   const int grid = ((S.n_chains + kCwChains - 1) / kCwChains) * S.n_psr;
@@ -1879,7 +1475,7 @@ hipError_t launch_std_cw_bwd(const StdDev &S, const double *x, hipStream_t s) {
 hipError_t launch_std_fwd(const StdDev &S, const double *x, hipStream_t s) {
   const int grid = S.n_chains * S.n_psr;
   if (grid == 0) return hipSuccess;
-  PS_DISPATCH(S.tp, k_std_fwd, grid, S, x);
+  PS_DISPATCH(S.tp, k_std_fwd, ELIM_WAVES, grid, S, x);
   return hipGetLastError();
 }
 
@@ -1887,7 +1483,7 @@ hipError_t launch_std_prior(const StdDev &S, const double *x, hipStream_t s) {
   if (S.nf_gw > 0) {
     const int grid = S.n_chains * S.nf_gw;
     if (S.split) hipLaunchKernelGGL(k_split_prior_g, dim3(grid), dim3(256), 0, s, S, x);
-    else PS_DISPATCH(S.tg, k_std_prior_dense, grid, S, x);
+    else PS_DISPATCH(S.tg, k_std_prior_dense, ELIM_WAVES, grid, S, x);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1900,7 +1496,7 @@ hipError_t launch_std_prior(const StdDev &S, const double *x, hipStream_t s) {
 hipError_t launch_std_bwd(const StdDev &S, const double *x, double *grad, hipStream_t s) {
   const int grid = S.n_chains * S.n_psr;
   if (grid == 0) return hipSuccess;
-  PS_DISPATCH(S.tp, k_std_bwd, grid, S, x, grad);
+  PS_DISPATCH(S.tp, k_std_bwd, ADJ_WAVES, grid, S, x, grad);
   return hipGetLastError();
 }
 
@@ -1909,8 +1505,8 @@ hipError_t launch_std_bwd(const StdDev &S, const double *x, double *grad, hipStr
 hipError_t launch_split_fwd(const StdDev &S, const double *x, hipStream_t s) {
   const int grid = S.n_chains * S.n_psr;
   if (grid == 0 || !S.split) return hipSuccess;
-  PS_DISPATCH(S.tpg, k_split_fac, grid, S, x, 0);
-  PS_DISPATCH(S.tpr, k_split_fac, grid, S, x, 1);
+  PS_DISPATCH(S.tpg, k_split_fac, ELIM_WAVES, grid, S, x, 0);
+  PS_DISPATCH(S.tpr, k_split_fac, ELIM_WAVES, grid, S, x, 1);
   hipLaunchKernelGGL(k_split_comb, dim3(grid), dim3(256), 0, s, S, x);
   return hipGetLastError();
 }
@@ -1920,9 +1516,9 @@ hipError_t launch_split_fwd(const StdDev &S, const double *x, hipStream_t s) {
 hipError_t launch_split_bwd(const StdDev &S, const double *x, double *grad, hipStream_t s) {
   const int grid = S.n_chains * S.n_psr;
   if (grid == 0 || !S.split) return hipSuccess;
-  PS_DISPATCH(S.tpg, k_split_bwd, grid, S, x, grad, 0);
-  PS_DISPATCH(S.tpr, k_split_bwd, grid, S, x, grad, 1);
-  PS_DISPATCH(S.tp, k_split_bwd_c, grid, S, x);
+  PS_DISPATCH(S.tpg, k_split_bwd, ADJ_WAVES, grid, S, x, grad, 0);
+  PS_DISPATCH(S.tpr, k_split_bwd, ADJ_WAVES, grid, S, x, grad, 1);
+  PS_DISPATCH(S.tp, k_split_bwd_c, ADJ_WAVES, grid, S, x);
   return hipGetLastError();
 }
 

@@ -12,7 +12,6 @@ namespace ps {
 
 constexpr double kLn10 = 2.30258509299404568401799145468;
 constexpr double kLn2Pi = 1.83787706640934548356065947281;
-constexpr int kThreads = 256;                    // threads per problem workgroup
 constexpr int kMaxTiles = 8;                     // 16-wide tiles per dimension (128)
 constexpr int kMaxRhoK = 32;                     // frequencies of the common process (>= PTAFS_MAX_HARM)
 constexpr int kMaxCw2 = 2 * PTAFS_MAX_CW_HARM;   // coefficients of the deterministic basis
@@ -70,7 +69,8 @@ struct StdDev {
   int n_chains;
   const double *beta;            // [n_chains] or nullptr (1)
   // workspace
-  double *xinv;                  // [n_chains][n_psr][ntiles(tp)][256] inverse of the reversed precision's factor
+  double *xinv;                  // [n_chains][n_psr][ntiles(tp) 256] X, the inverse of the reversed precision's factor,
+                                 // by block columns (el::store_x)
   double *avec;                  // [n_chains][n_psr][pp] a, original order
   double *ahat;                  // [n_chains][n_psr][pp] a_hat, reversed order
   double *v1;                    // [n_chains][n_psr][pp] beta (d - S0 a), reversed order
@@ -93,7 +93,7 @@ struct StdDev {
   double *dcw;                   // [n_chains][n_psr][8] the pulsar's part of dlog p / d theta_cw
   // split coefficients (set b: 0 common, 1 pulsar noise; vectors in the set's
   // original row order, strides ppg / ppr)
-  double *xg, *xr;               // [n_chains][n_psr][ntiles(tpg|tpr)][256] X of each set's reversed precision
+  double *xg, *xr;               // [n_chains][n_psr][ntiles(tpg|tpr) 256] X of each set's reversed precision
   double *lzg, *lzr;             // L_b z_b
   double *ag, *ar;               // a_G, a_R
   double *v2r;                   // -phi_R^-1 a_R (the common set's prior term goes to v2)
@@ -156,7 +156,6 @@ struct StdKick {
 }  // namespace ps
 
 namespace psk {
-hipError_t init_attributes();
 hipError_t launch_std_fwd(const ps::StdDev &S, const double *x, hipStream_t s);
 hipError_t launch_std_prior(const ps::StdDev &S, const double *x, hipStream_t s);
 hipError_t launch_std_bwd(const ps::StdDev &S, const double *x, double *grad, hipStream_t s);

@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <thread>
 #include <vector>
@@ -82,9 +81,6 @@ int drop_graph(ptafs_std *ds) {
   ds->graph = nullptr;
   return PTAFS_OK;
 }
-
-std::once_flag g_attr_once;
-hipError_t g_attr_err = hipSuccess;
 
 // ---------------------------------------------------------------- layout ---
 int plan(const ptafs_std_desc *d, ps::StdDev &B, int64_t &ntoa) {
@@ -607,8 +603,7 @@ int ptafs_std_create(const ptafs_std_desc *d, void *stream, ptafs_std **out) {
     delete ds;
     return PTAFS_E_HIP;
   }
-  std::call_once(g_attr_once, [] { g_attr_err = psk::init_attributes(); });
-  if (g_attr_err != hipSuccess || ptr::device_pool(ds->device, &ds->pool, &ds->aux) ||
+  if (ptr::device_pool(ds->device, &ds->pool, &ds->aux) ||
       hipEventCreateWithFlags(&ds->done, hipEventDisableTiming) != hipSuccess) {
     free_all(ds);
     return PTAFS_E_HIP;
