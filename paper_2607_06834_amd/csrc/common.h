@@ -83,18 +83,17 @@ constexpr int kHmcBeginG = 4;
 // Packed lower-triangular storage, row-major: row i holds columns 0..i.
 __host__ __device__ inline int pk(int i, int j) { return (i * (i + 1)) / 2 + j; }
 
-// Dense per-frequency factors: up to kTileMaxNT 16-row tiles they are kept
-// tile-major (the lower tiles of the padded matrix, 256 doubles each, row-major
-// inside a tile); beyond that packed row-major.
-// The tiled factorisation (k_cholt_fwd) holds up to kTileFwdMaxNT tiles in
-// registers; the tiled adjoint (k_cholt_bwd) all of C^-1 up to kTileMaxNT
-// tiles, one block column of it (the rest in LDS) up to kTileFwdMaxNT.
+// Dense per-frequency factors: up to kTileMaxNT 16-row tiles k_cholt factorises
+// them and takes their adjoint (one wave and two), beyond k_cholw (four waves).
+// Up to kTileStoreNT tiles a factor is kept tile-major (the lower tiles of the
+// padded matrix, 256 doubles each, row-major inside a tile), beyond packed
+// row-major.
 constexpr int kTileMaxNT = 5;
-constexpr int kTileFwdMaxNT = 7;
+constexpr int kTileStoreNT = 7;
 __host__ __device__ inline int chol_tiles(int n) { return (n + 15) / 16; }
 __host__ __device__ inline size_t chol_store_doubles(int n) {
   const int nt = chol_tiles(n);
-  return nt <= kTileFwdMaxNT ? (size_t)(nt * (nt + 1) / 2) * 256 : (size_t)n * (n + 1) / 2;
+  return nt <= kTileStoreNT ? (size_t)(nt * (nt + 1) / 2) * 256 : (size_t)n * (n + 1) / 2;
 }
 
 // ---------------------------------------------------------------------------
@@ -126,10 +125,9 @@ struct Dev {
   // (zeros in the padding) and sum_i ln N_i
   const double *invn;
   double lnn_total;
-  const double *pos, *gamma;
-  const double *gchol;         // chol(Gamma), packed row-major lower
-  const double *gtile;         // chol(Gamma) zero-padded, lower 16x16 tiles (up to kTileFwdMaxNT)
-  const double *gam_tile;      // Gamma zero-padded, lower 16x16 tiles stored column-major, diagonal tiles full (up to kTileFwdMaxNT)
+  const double *pos;
+  const double *gtile;         // chol(Gamma) zero-padded, lower 16x16 tiles
+  const double *gam_tile;      // Gamma zero-padded, lower 16x16 tiles stored column-major, diagonal tiles full
   const double *prior_lo, *prior_hi;
   // power-law spectra: ln(f_k yr) for f_k = (k + 1) / T, k < PTAFS_MAX_HARM, and ln(yr^3 / (12 pi^2 T))
   const double *lnfy;
@@ -158,7 +156,7 @@ struct Dev {
   double *ddm_k;               // [c_pad][n_psr][nf_dm][2]
 
   int32_t *flag_k;             // [c_pad][kmax] kFlagNotPD of the diagonal frequencies (k_spec_fwd)
-  int32_t *flag_dense;         // [c_pad][nf_gw] kFlagNotPD of the dense frequencies (k_cholt/k_chol)
+  int32_t *flag_dense;         // [c_pad][nf_gw] kFlagNotPD of the dense frequencies (k_cholt / k_cholw)
   int32_t *flag_out;           // [c_pad][kmax + kSpecSeg] kFlagOutNonfinite of the adjoints:
                                //   [k] dense frequency k (k < nf_gw), [kmax + seg] k_spec_bwd segment
   int32_t *st_pre;             // [c_pad] status from the input checks
@@ -296,8 +294,8 @@ hipError_t launch_spec_fwd(const pt::Dev &D, const double *x, hipStream_t s);
 hipError_t launch_toa_mfma(const pt::Dev &D, int waves_per_block, int xcd_map, hipStream_t s);
 hipError_t launch_toa_plain_psr(const pt::Dev &D, int p, int n_chunks_p, hipStream_t s);
 hipError_t set_plain_lds_limit(size_t bytes);
-hipError_t launch_chol_fwd(const pt::Dev &D, const double *x, hipStream_t s);
-hipError_t launch_chol_bwd(const pt::Dev &D, const double *x, double *grad, hipStream_t s);
+hipError_t launch_cholw_fwd(const pt::Dev &D, const double *x, hipStream_t s);
+hipError_t launch_cholw_bwd(const pt::Dev &D, const double *x, double *grad, hipStream_t s);
 hipError_t launch_cholt_fwd(const pt::Dev &D, const double *x, hipStream_t s);
 hipError_t launch_cholt_bwd(const pt::Dev &D, const double *x, double *grad, hipStream_t s);
 hipError_t launch_reduce_chunks(const pt::Dev &D, hipStream_t s);

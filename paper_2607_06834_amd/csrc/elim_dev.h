@@ -98,12 +98,12 @@ __device__ inline double rsqrt_c(double a) {
 // below.  The instructions issued set the time of a lone wave: 16 pivots one by
 // one, each with its row broadcast to the lane rows, took 60 instructions and
 // 310 cycles a pivot, 5.0e3 cycles a tile.
-// rs[j] (LDS) receives 1 / L_jj = X_jj.  With LZ, lzd[c] = (L z)_c (LDS), z the
-// second of the pair tz.  ok is cleared in the lanes that see a pivot that is
+// rs[j] (LDS) receives 1 / L_jj = X_jj.  With LZ, the pair lzd[c] = (L tz)_c
+// (LDS).  r receives L^T.  ok is cleared in the lanes that see a pivot that is
 // not positive and finite.
 template <bool LZ>
 __device__ __forceinline__ v4d diag(v4d n, bool &ok, int c, int q, double *scr, double *rs, const double *tz,
-                                    double *lzd) {
+                                    double *lzd, v4d &r) {
   // opaque to the compiler, which would otherwise keep the lane masks below in
   // scalar registers across the caller's loop (and spill them)
   asm volatile("" : "+v"(c), "+v"(q));
@@ -149,15 +149,15 @@ __device__ __forceinline__ v4d diag(v4d n, bool &ok, int c, int q, double *scr, 
     f = __builtin_amdgcn_mfma_f64_4x4x4f64(u, f, 0.0, 0, 0, 0);
     e[b] = f;
     if (q == 0 && c < 4) rs[4 * b + c] = ri;
-    if (LZ)
-      part = __builtin_amdgcn_mfma_f64_4x4x4f64(tz[2 * (4 * b + q) + (c & 1)], c >= 4 * b + q ? s : 0.0, part, 0, 0, 0);
+    r[b] = c >= 4 * b + q ? s : 0.0;
+    if (LZ) part = __builtin_amdgcn_mfma_f64_4x4x4f64(tz[2 * (4 * b + q) + (c & 1)], r[b], part, 0, 0, 0);
     if (b < 3) {
       const double sm = (c >= 4 * b + 4) ? s : 0.0;   // the rows below the strip
       n = __builtin_amdgcn_mfma_f64_16x16x4f64(sm, s, n, 0, 0, 0);
       e = __builtin_amdgcn_mfma_f64_16x16x4f64(sm, f, e, 0, 0, 0);
     }
   }
-  if (LZ && q == 1) lzd[c] = part;
+  if (LZ && q < 2) lzd[2 * c + q] = part;
   return e;
 }
 
@@ -169,8 +169,12 @@ struct Lds {
   double xd[(W > 1 ? 2 : 1) * kTile];
   double scr[64];
   double rs[16 * T];    // 1 / L_jj
-  double lzd[16 * T];   // the diagonal tiles' part of L z
+  double lzd[32 * T];   // the diagonal tiles' part of L z
   __device__ inline double *xjj(int J) { return xd + (W > 1 ? (J & 1) * kTile : 0); }
+};
+
+struct NoSink {
+  static constexpr bool kOn = false;
 };
 
 template <int T, int W>
@@ -199,43 +203,48 @@ struct Elim {
   __device__ __forceinline__ bool has(int s) const { return (s + 1) * W <= NT || s * W + w < NT; }
 
   // factor and inverse of the diagonal tile n = -A_JJ; X_JJ to LDS
-  template <bool LZ>
-  __device__ __forceinline__ v4d pivot(const v4d &n, int J, Lds<T, W> &L, int *flag, const double *tv) {
+  template <bool LZ, class Sink>
+  __device__ __forceinline__ v4d pivot(const v4d &n, int J, Lds<T, W> &L, int *flag, const double *tv, Sink &sink) {
     bool ok = true;
-    const v4d x = diag<LZ>(n, ok, c, q, L.scr, L.rs + 16 * J, LZ ? tv + 32 * J : nullptr, L.lzd + 16 * J);
+    v4d r;
+    const v4d x = diag<LZ>(n, ok, c, q, L.scr, L.rs + 16 * J, LZ ? tv + 32 * J : nullptr, L.lzd + 32 * J, r);
     st_cm(L.xjj(J), c, q, x);
+    if constexpr (Sink::kOn) sink.diagonal(J, r);
     if (!__all(ok) && lane == 0) *flag = 0;
     return x;
   }
 
-  // The whole elimination of the slots' -A.  NB = 1 or 2 right-hand sides, the
-  // first NB of the pair bv ([16 T][2], LDS, consumed), give t = X b in the first
-  // NB of the pair tv.  With LZ (NB = 1) the second of tv is z, and L z is the
-  // second of bv (zero on entry) plus L.lzd.  hook(J) runs in step 3, when row J
-  // of X is complete (X_JC, C < J, at L.row + kTile C, X_JJ at L.xjj(J)).  flag
-  // (LDS) is cleared when a pivot fails.  All 64 W threads call it, after a
-  // barrier that follows the caller's writes of bv, tv and flag.
-  template <int NB, bool LZ, class Hook>
-  __device__ __forceinline__ void run(Lds<T, W> &L, int *flag, double *bv, double *tv, Hook hook) {
-    if (w == 0) a[0] = pivot<LZ>(a[0], 0, L, flag, tv);
+  // The whole elimination of the slots' -A.  Of the pairs bv and tv ([16 T][2],
+  // LDS) the first NB are right-hand sides b (consumed) and t = X b; the next
+  // NZ of tv are vectors z, and L z is theirs of bv (zero on entry) plus L.lzd.
+  // hook(J) runs in step 3, when row J of X is complete (X_JC, C < J, at
+  // L.row + kTile C, X_JJ at L.xjj(J)).  A sink takes the factor: diagonal(J,
+  // L_JJ^T) and below(I, J, rows q + 4 v of L_IJ).  INV false leaves X out (the
+  // factor, t and L z only).  flag (LDS) is cleared when a pivot fails.  All
+  // 64 W threads call it, after a barrier that follows the caller's writes of
+  // bv, tv and flag.
+  template <int NB, int NZ, bool INV = true, class Hook, class Sink = NoSink>
+  __device__ __forceinline__ void run(Lds<T, W> &L, int *flag, double *bv, double *tv, Hook hook, Sink sink = Sink()) {
+    if (w == 0) a[0] = pivot<(NZ > 0)>(a[0], 0, L, flag, tv, sink);
     __syncthreads();
     if constexpr (W == 1 && T <= 4) {   // one wave: the tiles of each step are known
 #pragma unroll
-      for (int J = 0; J < T; ++J) step<NB, LZ>(J, L, flag, bv, tv, hook);
+      for (int J = 0; J < T; ++J) step<NB, NZ, INV>(J, L, flag, bv, tv, hook, sink);
     } else {
 #pragma unroll 1
       for (int J = 0; J < T; ++J) {
         // opaque in the loop, so that the addresses formed from the tiles are
         // not kept in registers across it
         if (W > 1) asm volatile("" : "+s"(ti), "+s"(tc));
-        step<NB, LZ>(J, L, flag, bv, tv, hook);
+        step<NB, NZ, INV>(J, L, flag, bv, tv, hook, sink);
       }
     }
   }
 
-  template <int NB, bool LZ, class Hook>
-  __device__ __forceinline__ void step(int J, Lds<T, W> &L, int *flag, double *bv, double *tv, Hook hook) {
-    constexpr bool kVec = NB > 0 || LZ;
+  template <int NB, int NZ, bool INV, class Hook, class Sink>
+  __device__ __forceinline__ void step(int J, Lds<T, W> &L, int *flag, double *bv, double *tv, Hook &hook, Sink &sink) {
+    static_assert(NB + NZ <= 2, "one pair of vectors");
+    constexpr bool kVec = NB + NZ > 0, LZ = NZ > 0;
     double *xj = L.xjj(J);
     // 2. row J
     {
@@ -243,9 +252,11 @@ struct Elim {
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int I = tile_i(s), C = tile_c(s);
-        if ((I == J) != (C == J) && has(s)) {
+        if ((INV ? (I == J) != (C == J) : (I != J && C == J)) && has(s)) {
           const v4d r = ln::mfma4(xn, a[s], v4d{0.0, 0.0, 0.0, 0.0});
           st_cm(L.row + kTile * (I == J ? C : I), c, q, r);
+          if constexpr (Sink::kOn)
+            if (C == J) sink.below(I, J, ld_rm(L.row + kTile * I, c, q));
           a[s] = r;
           if (C == J) a[s] = v4d{0.0, 0.0, 0.0, 0.0};   // Y_IJ starts in step 3
         }
@@ -267,7 +278,7 @@ struct Elim {
       for (int s = 0; s < NS; ++s)
         if (s == sd) d = a[s];
       const v4d r = ld_cm(L.row + kTile * (J + 1), c, q);
-      const v4d x = pivot<LZ>(ln::mfma4(r, r, d), J + 1, L, flag, tv);
+      const v4d x = pivot<LZ>(ln::mfma4(r, r, d), J + 1, L, flag, tv, sink);
 #pragma unroll
       for (int s = 0; s < NS; ++s)
         if (s == sd) a[s] = x;
@@ -282,15 +293,15 @@ struct Elim {
     operands(NS - 1, J, L, xj, u, v);
 #pragma unroll
     for (int s = NS - 1; s >= 0; --s) {
-      v4d un, vn;
+      v4d un{}, vn{};
       if (has(s)) {
         if (tile_i(s) <= J) break;
         if (s > 0) operands(s - 1, J, L, xj, un, vn);
         if (s != sd) {
-          a[s] = ln::mfma4(u, v, a[s]);
-          if (kVec && tile_c(s) == J) {   // b -= R_JI^T t and L z += R_JI^T z
+          if (INV || tile_c(s) > J) a[s] = ln::mfma4(u, v, a[s]);
+          if (kVec && tile_c(s) == J) {   // b -= R_JI^T t, L z += R_JI^T z
             const double e = pair_tdot(ty, u);
-            if (q < (LZ ? 2 : NB)) {
+            if (q < NB + NZ) {
               double *o = bv + 2 * (16 * tile_i(s) + c) + q;
               *o = q < NB ? *o - e : *o + e;
             }
@@ -306,7 +317,7 @@ struct Elim {
       const int s1 = ps::tix(J + 1, J + 1);
 #pragma unroll
       for (int s = 0; s < NS; ++s)
-        if (s == s1) a[s] = pivot<LZ>(a[s], J + 1, L, flag, tv);
+        if (s == s1) a[s] = pivot<LZ>(a[s], J + 1, L, flag, tv, sink);
     }
     __syncthreads();
   }

@@ -1,8 +1,7 @@
 // Dense per-frequency prior covariance on FP64 matrix cores: one 64-lane wave
 // per (frequency, chain) holds the lower 16x16 tiles of the padded matrix in
-// registers.  The factorisation takes arrays of up to 112 pulsars (seven
-// tiles), the adjoint up to 80 (five tiles; beyond that k_chol's adjoint reads
-// the same tile-major factor).
+// registers, for arrays of up to 80 pulsars (five tiles); k_cholw takes the
+// larger ones.
 //
 // Forward (Sec. IV.A, Eqs. HD, prior_cov; Sec. II.B, Eq.
 // standardizing_transform with mu = 0): C = chol(rho_k Gamma + diag kappa_.k)
@@ -35,6 +34,7 @@
 // consecutive rows 4q .. 4q + 3 of every tile.
 #include "common.h"
 #include "lane_dev.h"
+#include "quad_dev.h"
 #include "spec_dev.h"
 
 namespace {
@@ -52,39 +52,16 @@ using ln::v4d;
 using ln::wave_sync;
 using ln::xor16_d;
 using ln::xor32_d;
+using qf::load_rows;
+using qf::pi16;
+using qf::scan_rows;
+using qf::ScanState;
 
 __host__ __device__ constexpr int tidx(int I, int J) { return I * (I + 1) / 2 + J; }
 
 // independent (frequency, chain) problems per workgroup, one wave each
 constexpr int kProbPerGroup = 4;
 
-// Work of the extra workgroups: G = nb * ns workgroups (spec_groups_fwd,
-// spec_groups) for nb blocks of 16 chains and ns contiguous frequency
-// segments.  The forward's segments hold equal numbers of frequencies (a
-// split by the parts a frequency carries was measured slower); the adjoint's
-// segments are balanced by cost, a frequency costing one unit per part it
-// carries (diagonal red noise, DM).
-struct spec_split {
-  int G, nb, ns, kmax, nf_gw, ka, nf_dm;
-  bool by_cost;
-  __device__ spec_split(const Dev &D, int groups, int chains, bool balanced)
-      : G(groups), nb((chains + pt::kCB - 1) / pt::kCB), ns(max(1, groups / nb)),
-        kmax(max(D.ka, D.nf_dm)), nf_gw(D.nf_gw), ka(D.ka), nf_dm(D.nf_dm), by_cost(balanced) {}
-  __device__ int cost(int k) const { return (k >= nf_gw && k < ka ? 1 : 0) + (k < nf_dm ? 1 : 0); }
-  // first frequency of segment s (every segment keeps at least one: ns <= kmax)
-  __device__ int k_lo(int s) const {
-    if (s <= 0) return 0;
-    if (s >= ns) return kmax;
-    if (!by_cost) return kmax * s / ns;
-    int total = 0;
-    for (int k = 0; k < kmax; ++k) total += cost(k);
-    int run = 0, k = 0;
-    while (k < kmax && (long long)run * ns < (long long)total * s) run += cost(k++);
-    return min(max(k, s), kmax - (ns - s));
-  }
-};
-
-__device__ inline int pi16(int c) { return 4 * (c & 3) + (c >> 2); }
 
 // ---------------------------------------------------------------------------
 // Forward: one wave per (frequency, chain) problem, nf_gw * c_pad problems.
@@ -93,7 +70,7 @@ template <int NT>
 __global__ __launch_bounds__(64 * kProbPerGroup) void k_cholt_fwd(Dev D, const double *__restrict__ x,
                                                                   int n_dense_groups) {
   if ((int)blockIdx.x >= n_dense_groups) {   // diagonal frequencies
-    const spec_split sp(D, gridDim.x - n_dense_groups, D.c_pad, false);
+    const pt::spec_split sp(D, gridDim.x - n_dense_groups, D.c_pad, false);
     for (int it = blockIdx.x - n_dense_groups; it < sp.nb * sp.ns; it += sp.G) {
       const int b = it / sp.ns, s = it - b * sp.ns;
       pt::spec_fwd_cb(D, x, b * pt::kCB, sp.k_lo(s), sp.k_lo(s + 1), s, sp.ns);
@@ -312,89 +289,24 @@ __global__ __launch_bounds__(64 * kProbPerGroup) void k_cholt_fwd(Dev D, const d
 // ---------------------------------------------------------------------------
 // Backward: one wave per (frequency, chain) problem, nf_gw * n_chains problems.
 // ---------------------------------------------------------------------------
-struct ScanState {
-  double rs, rc, q;   // running column sums of z x (sin, cos) and the quadratic form
-};
-
-// One 16-row tile of 16 columns (B layout: item v of lane group q is row
-// row0 + 4q + v) added to the column quadratic forms x^T P x; vr[v] holds
-// (v_sin, v_cos, z_sin, z_cos) of row row0 + 4q + v.
-__device__ inline void scan_rows(const v4d &X, const double (&vr)[4][4], ScanState &st, int q) {
-  double ls = 0.0, lc = 0.0, part = 0.0, sa = 0.0, ca = 0.0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const double x = X[v];
-    const double bs = vr[v][2] * x, bc = vr[v][3] * x;
-    const double as = vr[v][0] * x, ac = vr[v][1] * x;
-    part += as * (ls + 0.5 * bs) + ac * (lc + 0.5 * bc);
-    ls += bs;
-    lc += bc;
-    sa += as;
-    ca += ac;
-  }
-  // inclusive prefix of the lane sums over the four lane groups of a column
-  // and their total, by the row swaps: with t the partner row's sum, the
-  // pair total is p = x + t, the prefix x (+ t on odd rows) (+ the other
-  // half's pair total on rows 2 and 3), the total p + that
-  const double ts1 = xor16_d(ls, q), tc1 = xor16_d(lc, q);
-  const double ps = ls + ts1, pc2 = lc + tc1;
-  const double os = xor32_d(ps, q), oc = xor32_d(pc2, q);
-  double is = (q & 1) ? ps : ls, ic = (q & 1) ? pc2 : lc;
-  if (q >= 2) {
-    is += os;
-    ic += oc;
-  }
-  const double ts = ps + os, tc = pc2 + oc;
-  st.q += part + (st.rs + (is - ls)) * sa + (st.rc + (ic - lc)) * ca;
-  st.rs += ts;
-  st.rc += tc;
-}
-
-// this lane's rows of v and z for the row tile at row0
-__device__ inline void load_rows(const double (*vz)[4], int row0, int q, double (&vr)[4][4]) {
-#pragma unroll
-  for (int v = 0; v < 4; ++v)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) vr[v][k] = vz[row0 + 4 * q + v][k];
-}
-
-__device__ inline void scan_tile(const v4d &X, int row0, const double (*vz)[4], ScanState &st,
-                                 int l, int c16, int q) {
-  double vr[4][4];
-  load_rows(vz, row0, q, vr);
-  scan_rows(X, vr, st, q);
-}
-
-// Up to kTileMaxNT tiles all of W = C^-1 lives in registers and a problem
-// has two waves, kBwdProbs problems per workgroup: wave 0 of a problem forms
+// All of W = C^-1 lives in registers and a problem has two waves, kBwdProbs problems per workgroup: wave 0 of a problem forms
 // v = C^T abar and then the d/dkappa quadratic forms, wave 1 the diagonal
 // inverses and W and then M = W G and the d/drho forms (the two halves are
-// independent until W and v meet in LDS), at two waves a SIMD.  Beyond
-// (COLW) the workgroup is one wave and one problem: W is built one block
-// column at a time in registers and kept in LDS (the diagonal inverses in
-// place of the diagonal tiles of C).
-constexpr int kBwdProbs = 2;
-template <int NT>
-constexpr int bwd_probs() { return NT > pt::kTileMaxNT ? 1 : kBwdProbs; }
-template <int NT>
-constexpr int bwd_wpp() { return NT > pt::kTileMaxNT ? 1 : 2; }   // waves per problem
-template <int NT>
-constexpr int bwd_threads() { return 64 * bwd_probs<NT>() * bwd_wpp<NT>(); }
+// independent until W and v meet in LDS), at two waves a SIMD.
+constexpr int kBwdProbs = 2, kBwdThreads = 128 * kBwdProbs;
 
 template <int NT>
-__global__ __launch_bounds__(bwd_threads<NT>()) __attribute__((amdgpu_waves_per_eu(bwd_wpp<NT>())))
+__global__ __launch_bounds__(kBwdThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void k_cholt_bwd(Dev D, const double *__restrict__ x,
                                                   double *__restrict__ grad,
                                                   const double *__restrict__ lst,
                                                   const double *__restrict__ gch,
                                                   const double *__restrict__ bar,
                                                   int n_dense_groups) {
-  constexpr bool COLW = NT > pt::kTileMaxNT;
-  constexpr int PPG = bwd_probs<NT>();
-  constexpr int WPP = bwd_wpp<NT>();
-  static_assert(COLW || bwd_threads<NT>() == 256, "the diagonal-frequency work runs on 256 threads");
+  constexpr int PPG = kBwdProbs;
+  static_assert(kBwdThreads == 256, "the diagonal-frequency work runs on 256 threads");
   if ((int)blockIdx.x >= n_dense_groups) {   // diagonal frequencies
-    const spec_split sp(D, gridDim.x - n_dense_groups, D.n_chains, true);
+    const pt::spec_split sp(D, gridDim.x - n_dense_groups, D.n_chains, true);
     for (int it = blockIdx.x - n_dense_groups; it < sp.nb * sp.ns; it += sp.G) {
       const int b = it / sp.ns, s = it - b * sp.ns;
       pt::spec_bwd_cb(D, x, grad, b * pt::kCB, sp.k_lo(s), sp.k_lo(s + 1), s, sp.ns);
@@ -405,14 +317,14 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
   constexpr int NP = 16 * NT;
   constexpr int NTILE = NT * (NT + 1) / 2;
   constexpr int TS = 17;                              // LDS row stride of a tile
-  constexpr int NTL = COLW ? NTILE : (NTILE > 2 * NT ? NTILE : 2 * NT);
+  constexpr int NTL = NTILE > 2 * NT ? NTILE : 2 * NT;
   __shared__ double vz_[PPG][NP][4];                   // v_sin, v_cos, z_sin, z_cos
   __shared__ double tl_[PPG][NTL][16 * TS];
   __shared__ double ab_[PPG][NP][2];
   __shared__ int nbad_[PPG];
-  const int w = (threadIdx.x >> 6) / WPP;          // problem slot
-  const int role = (threadIdx.x >> 6) - w * WPP;   // 0: v and d/dkappa, 1: W and d/drho
-  const bool do_v = COLW || role == 0;
+  const int w = (threadIdx.x >> 6) >> 1;        // problem slot
+  const int role = (threadIdx.x >> 6) & 1;      // 0: v and d/dkappa, 1: W and d/drho
+  const bool do_v = role == 0;
   const int prob = blockIdx.x * PPG + w;
   if (prob >= D.nf_gw * D.n_chains) return;
   const int k0 = prob % D.nf_gw, c = prob / D.nf_gw;
@@ -450,7 +362,7 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
   const double lnfy = D.lnfy[k0];   // for the outputs (loaded here, not after the barriers)
   const double *Cb = lst + ((size_t)c * D.nf_gw + k0) * (NTILE * 256);
   const int pc = pi16(c16);
-  if constexpr (!COLW) {
+  {
     if (role == 1) {
       // ==== wave 1: W = C^-1, then M = W G and the d/drho quadratic forms
       const double rho_o = pt::powerlaw_k(D, k0, xc[D.off_gw], xc[D.off_gw + 1]);
@@ -571,7 +483,7 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
       return;
     }
   }
-  // ==== wave 0 (the only wave in the column-wise form): v = C^T abar, then
+  // ==== wave 0: v = C^T abar, then
   //      the d/dkappa quadratic forms and the pulsars' outputs
   // the spectra for the outputs, early (their loads and exponentials overlap the work below)
   double kapo[2];
@@ -598,7 +510,7 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
   double vcol[NT][2];
 #pragma unroll
   for (int J = 0; J < NT; ++J) {
-    if constexpr (!COLW) __builtin_amdgcn_sched_barrier(0);   // one column's loads in flight at a time
+    __builtin_amdgcn_sched_barrier(0);   // one column's loads in flight at a time
     double ss = 0.0, sc = 0.0;
 #pragma unroll
     for (int K = J; K < NT; ++K) {
@@ -639,99 +551,7 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
   }
 
   double dkap[NT] = {};
-  double dr = 0.0;
-  if constexpr (COLW) {
-    // ---- inverses of the diagonal tiles, in place: lane group g solves
-    //      tile J = g (+4, ...) column c16 by forward substitution
-#pragma unroll
-    for (int J = 0; J < NT; ++J)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        tl[tidx(J, J)][(4 * q + v) * TS + c16] = Cb[tidx(J, J) * 256 + (4 * q + v) * 16 + c16];
-    wave_sync();
-#pragma unroll
-    for (int rnd = 0; rnd < (NT + 3) / 4; ++rnd) {
-      const int J = 4 * rnd + q;
-      if (J < NT) {
-        double *T = tl[tidx(J, J)];
-        double xs[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          __builtin_amdgcn_sched_barrier(0);   // bound the live LDS reads to one row
-          double s = (r == c16) ? 1.0 : 0.0;
-#pragma unroll
-          for (int m = 0; m < r; ++m) s -= T[r * TS + m] * xs[m];
-          xs[r] = s / T[r * TS + r];
-        }
-        // (the lanes of a group read all of C_JJ before any of them writes)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) T[r * TS + c16] = xs[r];
-      }
-    }
-    wave_sync();
-    // ---- W = C^-1 by block columns: W_IJ = -W_II sum_{J<=K<I} C_IK W_KJ
-    //      (B layout), the column's d/dkappa, then the column into LDS
-#pragma unroll
-    for (int J = 0; J < NT; ++J) {
-      __builtin_amdgcn_sched_barrier(0);       // one block column live at a time
-      v4d Wc[NT];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Wc[J][v] = tl[tidx(J, J)][(4 * q + v) * TS + c16];
-#pragma unroll
-      for (int I = J + 1; I < NT; ++I) {
-        __builtin_amdgcn_sched_barrier(0);
-        v4d U = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int K = J; K < I; ++K) {
-          v4d a;
-          const double *t = Cb + tidx(I, K) * 256 + pc * 16 + 4 * q;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) a[s] = t[s];
-          U = mfma4(a, Wc[K], U);
-        }
-        v4d wi;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) wi[s] = -tl[tidx(I, I)][pc * TS + 4 * q + s];
-        Wc[I] = mfma4(wi, U, v4d{0.0, 0.0, 0.0, 0.0});
-      }
-      ScanState st{0.0, 0.0, 0.0};
-#pragma unroll
-      for (int I = J; I < NT; ++I) scan_tile(Wc[I], 16 * I, vz, st, l, c16, q);
-      double qq = st.q;
-      qq += xor16_d(qq, q);
-      qq += xor32_d(qq, q);
-      dkap[J] = qq;
-#pragma unroll
-      for (int I = J + 1; I < NT; ++I)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) tl[tidx(I, J)][(4 * q + v) * TS + c16] = Wc[I][v];
-    }
-    wave_sync();
-    // ---- d/drho: M = W G column block by column block, W in A layout from LDS
-#pragma unroll
-    for (int J = 0; J < NT; ++J) {
-      ScanState st{0.0, 0.0, 0.0};
-#pragma unroll
-      for (int I = J; I < NT; ++I) {
-        __builtin_amdgcn_sched_barrier(0);     // one product tile live at a time
-        v4d Mt = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int K = J; K <= I; ++K) {
-          v4d a, g;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) a[s] = tl[tidx(I, K)][pc * TS + 4 * q + s];
-          const double *gt = gch + tidx(K, J) * 256 + 64 * q + c16;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) g[v] = gt[16 * v];
-          Mt = mfma4(a, g, Mt);
-        }
-        scan_tile(Mt, 16 * I, vz, st, l, c16, q);
-      }
-      dr += st.q;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dr += __shfl_xor(dr, o, 64);
-  } else {
+  {
     __syncthreads();   // W (wave 1) and v, z (this wave) of every problem in LDS
       // ---- d/dkappa: quadratic forms down the columns of W (B layout), row
       //      tile by row tile, so that each tile's rows of v and z are read once
@@ -781,42 +601,8 @@ void k_cholt_bwd(Dev D, const double *__restrict__ x,
     }
   }
   const int nbad = __popcll(__ballot(!fin));
-  if constexpr (!COLW) {
-    if (l == 0) nbad_[w] = nbad;
-    __syncthreads();   // read by wave 1, which writes d/drho and the flag
-  } else {
-    const double rho_o = pt::powerlaw_k(D, k0, xc[D.off_gw], xc[D.off_gw + 1]);
-    if (l == 0) {
-      dth[0] = dr * rho_o * 2.0 * pt::kLn10;
-      dth[1] = dr * rho_o * (-lnfy);
-      *fout = (nbad || !isfinite(dth[0]) || !isfinite(dth[1])) ? pt::kFlagOutNonfinite : 0;
-    }
-  }
-}
-
-// Workgroups for the diagonal-frequency work of `chains` chains next to ng
-// dense workgroups, `per_cu` of which fill a compute unit: the workgroup
-// slots those leave free, at least 8, split into blocks of 16 chains times
-// frequency segments (spec_split).
-int spec_groups(const Dev &D, int ng, int chains, int per_cu) {
-  const int nb = (chains + pt::kCB - 1) / pt::kCB;
-  const int kmax = max(D.ka, D.nf_dm);
-  const int ns = max(1, min(min(kmax, pt::kSpecSeg), max(8, per_cu * D.n_cu - ng) / nb));
-  return nb * ns;
-}
-
-// The forward's diagonal-frequency workgroups: up to one frequency segment
-// per frequency, four per free compute unit's worth (the forward's segments
-// write no per-segment flags, so their number is free).  A dense forward wave
-// leaves room for one more wave on its SIMD; with fewer, longer segments these
-// workgroups outlast the dense waves (measured: a segment of one or two
-// frequencies of 16 chains and 67 pulsars takes about 30k-60k cycles, a
-// dense wave about 48k).
-int spec_groups_fwd(const Dev &D, int ng, int chains) {
-  const int nb = (chains + pt::kCB - 1) / pt::kCB;
-  const int kmax = max(D.ka, D.nf_dm);
-  const int ns = max(1, min(kmax, 4 * max(8, D.n_cu - ng) / nb));
-  return nb * ns;
+  if (l == 0) nbad_[w] = nbad;
+  __syncthreads();   // read by wave 1, which writes d/drho and the flag
 }
 
 // grid: the dense problems, kProbPerGroup per workgroup, then the
@@ -825,21 +611,18 @@ template <int NT>
 hipError_t launch_fwd_t(const Dev &D, const double *x, hipStream_t s) {
   const int nprob = D.nf_gw * D.c_pad;
   const int ng = (nprob + kProbPerGroup - 1) / kProbPerGroup;
-  hipLaunchKernelGGL(k_cholt_fwd<NT>, dim3(ng + spec_groups_fwd(D, ng, D.c_pad)),
+  hipLaunchKernelGGL(k_cholt_fwd<NT>, dim3(ng + pt::spec_groups_fwd(D, ng, D.c_pad)),
                      dim3(64 * kProbPerGroup), 0, s, D, x, ng);
   return hipGetLastError();
 }
 
-// (beyond kTileMaxNT tiles the workgroups are single waves: the
-// diagonal-frequency work runs in its own launch, k_spec_bwd)
 template <int NT>
 hipError_t launch_bwd_t(const Dev &D, const double *x, double *grad, hipStream_t s) {
-  constexpr int P = bwd_probs<NT>();
   const int nprob = D.nf_gw * D.n_chains;
-  const int ng = (nprob + P - 1) / P;
+  const int ng = (nprob + kBwdProbs - 1) / kBwdProbs;
   // two tiled workgroups share a compute unit (half its LDS and registers each)
-  const int ns = NT > pt::kTileMaxNT ? 0 : spec_groups(D, ng, D.n_chains, 2);
-  hipLaunchKernelGGL(k_cholt_bwd<NT>, dim3(ng + ns), dim3(bwd_threads<NT>()), 0, s, D, x, grad,
+  const int ns = pt::spec_groups(D, ng, D.n_chains, 2);
+  hipLaunchKernelGGL(k_cholt_bwd<NT>, dim3(ng + ns), dim3(kBwdThreads), 0, s, D, x, grad,
                      (const double *)D.lstore, D.gtile, (const double *)D.bar_rn, ng);
   return hipGetLastError();
 }
@@ -855,8 +638,6 @@ hipError_t launch_cholt_fwd(const pt::Dev &D, const double *x, hipStream_t s) {
     case 3: return launch_fwd_t<3>(D, x, s);
     case 4: return launch_fwd_t<4>(D, x, s);
     case 5: return launch_fwd_t<5>(D, x, s);
-    case 6: return launch_fwd_t<6>(D, x, s);
-    case 7: return launch_fwd_t<7>(D, x, s);
   }
   return hipErrorInvalidValue;
 }
@@ -868,8 +649,6 @@ hipError_t launch_cholt_bwd(const pt::Dev &D, const double *x, double *grad, hip
     case 3: return launch_bwd_t<3>(D, x, grad, s);
     case 4: return launch_bwd_t<4>(D, x, grad, s);
     case 5: return launch_bwd_t<5>(D, x, grad, s);
-    case 6: return launch_bwd_t<6>(D, x, grad, s);
-    case 7: return launch_bwd_t<7>(D, x, grad, s);
   }
   return hipErrorInvalidValue;
 }

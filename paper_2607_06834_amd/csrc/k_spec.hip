@@ -4,7 +4,7 @@
 // whitening transforms (Sec. II.B, Eq. standardizing_transform, mu = 0) and
 // adjoints; the input checks, the timing-model rows of the coefficient
 // panels and the CW constants.  The frequencies that carry the common process (dense
-// phi_k = rho_k Gamma + diag kappa) are factorised in k_cholt / k_chol.
+// phi_k = rho_k Gamma + diag kappa) are factorised in k_cholt / k_cholw.
 //
 //   diagonal frequencies:  a_Ik = sqrt(kappa_Ik) z_Ik,  dz = sqrt(kappa) abar - z,
 //     d/dlog10A_I = ln10 sqrt(kappa) abar.z,  d/dgamma_I = -1/2 ln(f yr) sqrt(kappa) abar.z

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
   }
   __syncthreads();
   // X = L~^-1, t = X beta d~ and L~ z~
-  el.template run<1, true>(L, &flag, bv, tv, [](int) {});
+  el.template run<1, 1>(L, &flag, bv, tv, [](int) {});
   for (int r = tid; r < pp; r += NTH) tv[2 * r + 1] += tv[2 * r];
   __syncthreads();
   // a_hat~ = X^T t, a~ = X^T (t + z~)
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
     S.ahat[ci * pp + r] = sh;
     // beta (d - S0 a) in the reversed order: A~ a~ = L~ (t + z~) = beta d~ + L~ z~,
     // so beta S0~ a~ = beta d~ + L~ z~ - a~ / D~ and v1 = a~ / D~ - L~ z~
-    const double v1 = sa * vdi[r] - (bv[2 * r + 1] + L.lzd[r]);
+    const double v1 = sa * vdi[r] - (bv[2 * r + 1] + L.lzd[2 * r + 1]);
     S.v1[ci * pp + r] = v1;
     if (r < P) {
       S.avec[ci * pp + (P - 1 - r)] = sa;
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) v
   // X and y = X a for sin and cos; tr(phi^-1 Gamma) = |X G|_F^2, G = chol(Gamma),
   // row by row as X is formed: tiles (X G)_JK = sum_{M=K}^{J} X_JM G_MK
   double part_t = 0.0;
-  el.template run<2, false>(L, &flag, bv, tv, [&](int J) {
+  el.template run<2, 0>(L, &flag, bv, tv, [&](int J) {
     for (int K = (el.w + J) % W; K <= J; K += W) {
       v4d r{0.0, 0.0, 0.0, 0.0};
       for (int M = K; M <= J; ++M) {
@@ -1222,7 +1222,7 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_split_f
     }
   }
   __syncthreads();
-  el.template run<0, false>(L, &flag, nullptr, nullptr, [](int) {});
+  el.template run<0, 0>(L, &flag, nullptr, nullptr, [](int) {});
   double *part = L.row;
   el.xty(part, zv);
   el::store_x(el, (b ? S.xr : S.xg) + ci * (E::NT * 256));

@@ -547,10 +547,9 @@ size_t dataset_bytes_of(const pt::Dev &B, int n_chunks) {
   const size_t n = B.n_psr, ntoa = B.n_toa, npad = ntoa + pt::kToaPad;
   auto a = [](size_t count, size_t size) { return std::max<size_t>(count, 1) * size; };
   const int nt = pt::chol_tiles(B.n_psr);
-  const size_t ntile = (size_t)(nt * (nt + 1) / 2) * 256;
-  const size_t tiles = nt <= pt::kTileFwdMaxNT ? ntile : 0;
+  const size_t tiles = (size_t)(nt * (nt + 1) / 2) * 256;
   size_t b = 7 * a(npad, 8) + 2 * a(ntoa, 8) + a(ntoa, 4) + 2 * a(B.n_backend, 8) + a(n + 1, 8) +
-             2 * a(n, 8) + a(3 * n, 8) + a(n * n, 8) + a(n * (n + 1) / 2, 8) + 2 * a(tiles, 8) +
+             2 * a(n, 8) + a(3 * n, 8) + 2 * a(tiles, 8) +
              2 * a(B.n_theta, 8) + a(PTAFS_MAX_HARM, 8);
   b += (size_t)(3 * n_chunks + n + 1) * sizeof(int32_t);
   return b;
@@ -763,34 +762,28 @@ int ptafs_dataset_create(const ptafs_dataset_desc *d, void *stream, ptafs_datase
   chk(upload(ds, tc.data(), n, &B.tau_c, s));
   chk(upload(ds, tsi.data(), n, &B.tau_sinv, s));
   chk(upload(ds, d->psr_pos, (size_t)3 * n, &B.pos, s));
-  chk(upload(ds, gam.data(), (size_t)n * n, &B.gamma, s));
-  chk(upload(ds, gch.data(), gch.size(), &B.gchol, s));
   {
-    // the same factor as 16x16 tiles (tile (K, J) at K (K + 1) / 2 + J, row-major
-    // inside), for the matrix-core adjoint of small arrays
+    // chol(Gamma) as 16x16 tiles (tile (K, J) at K (K + 1) / 2 + J, row-major
+    // inside) for the adjoint, Gamma likewise for the forward
     const int nt = pt::chol_tiles(n);
-    if (nt <= pt::kTileFwdMaxNT) {
-      gt.assign((size_t)(nt * (nt + 1) / 2) * 256, 0.0);
-      for (int K = 0; K < nt; ++K)
-        for (int J = 0; J <= K; ++J)
-          for (int rr = 0; rr < 16; ++rr)
-            for (int cc = 0; cc < 16; ++cc) {
-              const int r = 16 * K + rr, k = 16 * J + cc;
-              if (r < n && k <= r) gt[(size_t)(K * (K + 1) / 2 + J) * 256 + rr * 16 + cc] = gch[pt::pk(r, k)];
-            }
-    }
+    gt.assign((size_t)(nt * (nt + 1) / 2) * 256, 0.0);
+    for (int K = 0; K < nt; ++K)
+      for (int J = 0; J <= K; ++J)
+        for (int rr = 0; rr < 16; ++rr)
+          for (int cc = 0; cc < 16; ++cc) {
+            const int r = 16 * K + rr, k = 16 * J + cc;
+            if (r < n && k <= r) gt[(size_t)(K * (K + 1) / 2 + J) * 256 + rr * 16 + cc] = gch[pt::pk(r, k)];
+          }
     chk(upload(ds, gt.data(), gt.size(), &B.gtile, s));
-    if (nt <= pt::kTileFwdMaxNT) {
-      ht.assign((size_t)(nt * (nt + 1) / 2) * 256, 0.0);
-      for (int K = 0; K < nt; ++K)
-        for (int J = 0; J <= K; ++J)
-          for (int rr = 0; rr < 16; ++rr)
-            for (int cc = 0; cc < 16; ++cc) {
-              const int r = 16 * K + rr, k = 16 * J + cc;
-              // column-major tiles (the register image of the forward's layout)
-              if (r < n && k < n) ht[(size_t)(K * (K + 1) / 2 + J) * 256 + cc * 16 + rr] = gam[(size_t)r * n + k];
-            }
-    }
+    ht.assign((size_t)(nt * (nt + 1) / 2) * 256, 0.0);
+    for (int K = 0; K < nt; ++K)
+      for (int J = 0; J <= K; ++J)
+        for (int rr = 0; rr < 16; ++rr)
+          for (int cc = 0; cc < 16; ++cc) {
+            const int r = 16 * K + rr, k = 16 * J + cc;
+            // column-major tiles (the register image of the forward's layout)
+            if (r < n && k < n) ht[(size_t)(K * (K + 1) / 2 + J) * 256 + cc * 16 + rr] = gam[(size_t)r * n + k];
+          }
     chk(upload(ds, ht.data(), ht.size(), &B.gam_tile, s));
   }
   {

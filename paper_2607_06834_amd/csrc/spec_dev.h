@@ -7,7 +7,7 @@
 // whitening transforms (Sec. II.B, Eq. standardizing_transform, mu = 0) and
 // adjoints; the input checks, the timing-model rows of the coefficient
 // panels and the CW constants.  The frequencies that carry the common process (dense
-// phi_k = rho_k Gamma + diag kappa) are factorised in k_cholt / k_chol.
+// phi_k = rho_k Gamma + diag kappa) are factorised in k_cholt / k_cholw.
 //
 //   diagonal frequencies:  a_Ik = sqrt(kappa_Ik) z_Ik,  dz = sqrt(kappa) abar - z,
 //     d/dlog10A_I = ln10 sqrt(kappa) abar.z,  d/dgamma_I = -1/2 ln(f yr) sqrt(kappa) abar.z
@@ -180,7 +180,7 @@ __device__ inline void spec_fwd_block(const Dev &D, const double *__restrict__ x
 
 // ---------------------------------------------------------------------------
 // Backward of chain c (< n_chains) over the diagonal and DM frequencies
-// k = k_first, k_first + k_step, ... (the dense ones are in k_cholt / k_chol);
+// k = k_first, k_first + k_step, ... (the dense ones are in k_cholt / k_cholw);
 // the non-finite flag goes to slot `slot` of the chain's segment flags.  One
 // block of 256 threads; every thread of the block calls it.
 // ---------------------------------------------------------------------------
@@ -660,6 +660,57 @@ __device__ inline void spec_bwd_cb(const Dev &D, const double *__restrict__ x,
     if (k_lo == 0)
       for (int s2 = nslot; s2 < kSpecSeg; ++s2) fo[s2] = 0;
   }
+}
+
+// Work of the extra workgroups: G = nb * ns workgroups (spec_groups_fwd,
+// spec_groups) for nb blocks of 16 chains and ns contiguous frequency
+// segments.  The forward's segments hold equal numbers of frequencies (a
+// split by the parts a frequency carries was measured slower); the adjoint's
+// segments are balanced by cost, a frequency costing one unit per part it
+// carries (diagonal red noise, DM).
+struct spec_split {
+  int G, nb, ns, kmax, nf_gw, ka, nf_dm;
+  bool by_cost;
+  __device__ spec_split(const Dev &D, int groups, int chains, bool balanced)
+      : G(groups), nb((chains + kCB - 1) / kCB), ns(max(1, groups / nb)),
+        kmax(max(D.ka, D.nf_dm)), nf_gw(D.nf_gw), ka(D.ka), nf_dm(D.nf_dm), by_cost(balanced) {}
+  __device__ int cost(int k) const { return (k >= nf_gw && k < ka ? 1 : 0) + (k < nf_dm ? 1 : 0); }
+  // first frequency of segment s (every segment keeps at least one: ns <= kmax)
+  __device__ int k_lo(int s) const {
+    if (s <= 0) return 0;
+    if (s >= ns) return kmax;
+    if (!by_cost) return kmax * s / ns;
+    int total = 0;
+    for (int k = 0; k < kmax; ++k) total += cost(k);
+    int run = 0, k = 0;
+    while (k < kmax && (long long)run * ns < (long long)total * s) run += cost(k++);
+    return min(max(k, s), kmax - (ns - s));
+  }
+};
+
+// Workgroups for the diagonal-frequency work of `chains` chains next to ng
+// dense workgroups, `per_cu` of which fill a compute unit: the workgroup
+// slots those leave free, at least 8, split into blocks of 16 chains times
+// frequency segments (spec_split).
+inline int spec_groups(const Dev &D, int ng, int chains, int per_cu) {
+  const int nb = (chains + kCB - 1) / kCB;
+  const int kmax = max(D.ka, D.nf_dm);
+  const int ns = max(1, min(min(kmax, kSpecSeg), max(8, per_cu * D.n_cu - ng) / nb));
+  return nb * ns;
+}
+
+// The forward's diagonal-frequency workgroups: up to one frequency segment
+// per frequency, four per free compute unit's worth (the forward's segments
+// write no per-segment flags, so their number is free).  A dense forward wave
+// leaves room for one more wave on its SIMD; with fewer, longer segments these
+// workgroups outlast the dense waves (measured: a segment of one or two
+// frequencies of 16 chains and 67 pulsars takes about 30k-60k cycles, a
+// dense wave about 48k).
+inline int spec_groups_fwd(const Dev &D, int ng, int chains) {
+  const int nb = (chains + kCB - 1) / kCB;
+  const int kmax = max(D.ka, D.nf_dm);
+  const int ns = max(1, min(kmax, 4 * max(8, D.n_cu - ng) / nb));
+  return nb * ns;
 }
 
 }  // namespace pt
