@@ -20,6 +20,7 @@
 #pragma once
 
 #include "common.h"
+#include "lane_dev.h"
 
 namespace pt {
 
@@ -91,9 +92,41 @@ __device__ inline void cw_constants(const double *th, const double *p, double ou
   }
 }
 
+// sin and cos of x, |x| < 2^40 (a phase beyond has no digits left): x less the
+// nearest multiple n of pi/2 by two fused steps (the two leading doubles of
+// pi/2), then the Taylor series to r^15 and r^16 on |r| <= pi/4, whose next
+// terms are below half a unit in the last place.  The library's sincos carries
+// the reduction of arguments of any size along, most of the instructions and
+// registers of the TOA pass's CW terms.
+__device__ inline void sincos_phase(double x, double &sn, double &cs) {
+  const double n = rint(x * 0.63661977236758134308);
+  double r = fma(-n, 1.57079632679489661923, x);
+  r = fma(-n, 6.123233995736766036e-17, r);
+  const double z = r * r;
+  double ps = -1.0 / 1307674368000.0, pc = 1.0 / 20922789888000.0;
+  ps = fma(ps, z, 1.0 / 6227020800.0);
+  ps = fma(ps, z, -1.0 / 39916800.0);
+  ps = fma(ps, z, 1.0 / 362880.0);
+  ps = fma(ps, z, -1.0 / 5040.0);
+  ps = fma(ps, z, 1.0 / 120.0);
+  ps = fma(ps, z, -1.0 / 6.0);
+  pc = fma(pc, z, -1.0 / 87178291200.0);
+  pc = fma(pc, z, 1.0 / 479001600.0);
+  pc = fma(pc, z, -1.0 / 3628800.0);
+  pc = fma(pc, z, 1.0 / 40320.0);
+  pc = fma(pc, z, -1.0 / 720.0);
+  pc = fma(pc, z, 1.0 / 24.0);
+  pc = fma(pc, z, -0.5);
+  const double s = fma(r * z, ps, r), c = fma(pc, z, 1.0);
+  const int k = (int)fma(-4.0, floor(0.25 * n), n);
+  const double a = (k & 1) ? c : s, b = (k & 1) ? s : c;
+  sn = (k & 2) ? -a : a;
+  cs = (k == 1 || k == 2) ? -b : b;
+}
+
 // Per-TOA state kept between the delay and its adjoint.
 struct CwToa {
-  double y, L1, E, alpha, s2P, c2P, h;
+  double y, ix, dEy, dEr, alpha, s2P, c2P, h;   // 1 / (1 - y), y E'(y), y E'(y) - E
 };
 
 // Constants of one (chain, pulsar) held in registers by a TOA-pass lane.
@@ -113,14 +146,35 @@ struct CwLane {
     s2s = b[kCwS2s * cp];
   }
 
+  // With u = (1 - y)^(1/8): alpha = a0 u, and since 1 - u^8 = y,
+  // v = u - 1 = -y / ((1 + u)(1 + u^2)(1 + u^4)) without cancellation, and so
+  // E = 1 - (1 - y)^(5/8) = 1 - (1 + v)^5 as a polynomial in v.  u comes from
+  // the 32-bit logarithm and exponential by one step of third order (the
+  // estimate's relative error, about 1e-7, cubed).  In place of log1p, expm1 and
+  // two exponentials.  For the adjoint, with E' = dE/dy = 5/8 u^-3 = 5/8 u^5 / (1 - y):
+  // y E' - E = u^-3 (5/8 - u^3 + 3/8 u^8) = v^2 u^-3 q(u), q the quotient by (u - 1)^2,
+  // again without the cancellation of the difference.
   __device__ inline CwToa delay(double t) const {
     CwToa s;
     s.y = K1 * t;
-    s.L1 = log1p(-s.y);                       // ln(1 - y)
-    s.E = -expm1(0.625 * s.L1);               // 1 - (1 - y)^(5/8)
-    const double Phi = phi0 + s.E * inv32X;
-    s.alpha = a0 * exp(0.125 * s.L1);
-    sincos(2.0 * Phi, &s.s2P, &s.c2P);
+    const double x = 1.0 - s.y;
+    s.ix = ln::rcp_nr(x);
+    const double u0 = (double)__builtin_amdgcn_exp2f(0.125f * __builtin_amdgcn_logf((float)x));
+    double u8 = u0 * u0;
+    u8 *= u8;
+    u8 *= u8;
+    const double e = fma(-u8, s.ix, 1.0);
+    const double u = fma(u0 * e, fma(e, 9.0 / 128.0, 0.125), u0);   // u0 (1 - e)^(-1/8)
+    const double u2 = u * u, u4 = u2 * u2;
+    const double v = -s.y * ln::rcp_nr((1.0 + u) * (1.0 + u2) * (1.0 + u4));
+    const double E = -v * fma(v, fma(v, fma(v, v + 5.0, 10.0), 10.0), 5.0);
+    const double Phi = fma(E, inv32X, phi0);
+    s.alpha = a0 * u;
+    const double im3 = u4 * u * s.ix;   // u^-3
+    s.dEy = 0.625 * s.y * im3;
+    const double qu = fma(u, fma(u, fma(u, fma(u, fma(u, fma(u, 0.375, 0.75), 1.125), 1.5), 1.875), 1.25), 0.625);
+    s.dEr = v * v * im3 * qu;
+    sincos_phase(2.0 * Phi, s.s2P, s.c2P);
     const double P = -s.s2P * (1.0 + ci * ci);
     const double Q = 2.0 * s.c2P * ci;
     s.h = -s.alpha * (P * U + Q * V);
@@ -135,13 +189,10 @@ struct CwLane {
     const double P = -s.s2P * opc, Q = 2.0 * s.c2P * ci;
     const double dP = -2.0 * s.c2P * opc, dQ = -4.0 * s.s2P * ci;     // d/dPhi
     const double dhPhi = -s.alpha * (dP * U + dQ * V);
-    const double omy = 1.0 - s.y;
-    const double dEdy = 0.625 * exp(-0.375 * s.L1);                  // 5/8 (1-y)^(-3/8)
-    const double t53 = (5.0 / 3.0) * s.E;
-    const double dPhiM = (dEdy * (5.0 / 3.0) * s.y - t53) * inv32X;    // dPhi/dln M
-    const double dPhiW = (dEdy * (8.0 / 3.0) * s.y - t53) * inv32X;    // dPhi/dln w0
-    const double dlaM = -(0.625 * s.y / omy) / 3.0;                   // dln alpha/dln M
-    const double dlaW = -2.0 / 3.0 - (1.0 / omy) / 3.0;               // dln alpha/dln w0
+    const double dPhiM = (5.0 / 3.0) * s.dEr * inv32X;               // dPhi/dln M
+    const double dPhiW = fma(5.0 / 3.0, s.dEr, s.dEy) * inv32X;      // dPhi/dln w0
+    const double dlaM = -(0.625 / 3.0) * s.y * s.ix;                   // dln alpha/dln M
+    const double dlaW = -2.0 / 3.0 - (1.0 / 3.0) * s.ix;               // dln alpha/dln w0
     const double sp = s.alpha * (P * c2s - Q * s2s);
     const double sx = s.alpha * (P * s2s + Q * c2s);
     acc[0] += g * sp;
