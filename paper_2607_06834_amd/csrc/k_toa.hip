@@ -56,13 +56,13 @@ __device__ inline int xcd_remap(int b, int G) {
 // register sets: two waves per SIMD, one with the CW terms.  (A single wave
 // leaves the matrix core idle about half the time.)
 template <int JTR, int JTD, int WPB, bool CW>
-__global__ __launch_bounds__(64 * WPB, CW ? (WPB == 4 ? 2 : 1) : (WPB == 4 ? 3 : 2))
+__global__ __launch_bounds__(64 * WPB, CW ? 2 : (WPB == 4 ? 3 : 2))
 void k_toa_mfma(Dev D, int xcd_map) {
   constexpr int NSR = 4 * JTR;
   constexpr int NSD = 4 * JTD;
   constexpr int ROWS = 16 * JTR;
   constexpr int FS = ROWS + 1;                 // padded LDS row stride (doubles)
-  constexpr bool SHB = WPB == 4;
+  constexpr bool SHB = WPB >= 4;
   __shared__ double ftab[WPB][16 * FS];
   __shared__ double cred[WPB][16];
   __shared__ double cwred[CW ? WPB : 1][8][16];
@@ -324,13 +324,13 @@ void k_toa_mfma(Dev D, int xcd_map) {
       }
     }
     __syncthreads();
-    if (wv == 0) {
-      for (int e = lane; e < ROWS * 16; e += 64) {
-        double s = ftab[0][e];
+    for (int e = threadIdx.x; e < ROWS * 16; e += 64 * WPB) {
+      double s = ftab[0][e];
 #pragma unroll
-        for (int w = 1; w < WPB; ++w) s += ftab[w][e];
-        pr[e] = s;
-      }
+      for (int w = 1; w < WPB; ++w) s += ftab[w][e];
+      pr[e] = s;
+    }
+    if (wv == 0) {
       if (lane < 16) {
         double s = cred[0][lane];
 #pragma unroll
@@ -357,13 +357,11 @@ void k_toa_mfma(Dev D, int xcd_map) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) ftab[wv][(16 * t + q + 4 * v) * 16 + col] = ad[t][v];
       __syncthreads();
-      if (wv == 0) {
-        for (int e = lane; e < 16 * JTD * 16; e += 64) {
-          double s = ftab[0][e];
+      for (int e = threadIdx.x; e < 16 * JTD * 16; e += 64 * WPB) {
+        double s = ftab[0][e];
 #pragma unroll
-          for (int w = 1; w < WPB; ++w) s += ftab[w][e];
-          pd[e] = s;
-        }
+        for (int w = 1; w < WPB; ++w) s += ftab[w][e];
+        pd[e] = s;
       }
     }
   }
@@ -619,6 +617,7 @@ hipError_t launch_toa_mfma(const pt::Dev &D, int wpb, int xcd, hipStream_t s) {
     case 1: return launch_mfma_r<1>(D, xcd, s);
     case 2: return launch_mfma_r<2>(D, xcd, s);
     case 4: return launch_mfma_r<4>(D, xcd, s);
+    case 8: return launch_mfma_r<8>(D, xcd, s);
   }
   return hipErrorInvalidValue;
 }

@@ -29,6 +29,7 @@ struct ptafs_dataset {
   hipStream_t aux = nullptr;          // library stream of the device (tuning changes, release)
   hipEvent_t done = nullptr;          // recorded after the data set's last enqueued work
   // tuning and chunk table of the TOA pass
+  int max_chunk_tiles = 0;
   int tiles_per_chunk = kDefaultTilesPerChunk, wpb = 1, xcd_map = 1;
   bool chunks_dirty = true;
   int32_t *d_chunk = nullptr;
@@ -278,6 +279,8 @@ void build_chunks(ptafs_dataset *ds, std::vector<int32_t> &tab) {
   }
   first[n] = (int32_t)cps.size();
   ds->n_chunks = (int)cps.size();
+  ds->max_chunk_tiles = 0;
+  for (size_t i = 0; i < cbg.size(); ++i) ds->max_chunk_tiles = std::max(ds->max_chunk_tiles, (cen[i] - cbg[i] + 15) / 16);
   tab.clear();
   tab.insert(tab.end(), cps.begin(), cps.end());
   tab.insert(tab.end(), cbg.begin(), cbg.end());
@@ -290,6 +293,22 @@ void build_chunks(ptafs_dataset *ds, std::vector<int32_t> &tab) {
       ds->wgmap_off[ncb] = (int)tab.size();
       tab.insert(tab.end(), map.begin(), map.end());
     }
+}
+
+// Waves per workgroup of the TOA pass: the tuning's, and up to eight for a data
+// set whose chunks would otherwise have fewer waves than there are compute
+// units (in one block of 16 chains: the rule must not look at the number of
+// chains, on which a chain's result does not depend), as long as every wave of
+// the longest chunk has a tile.  The chunk's waves are combined in LDS, so
+// neither the chunks nor the partials change.  Three pulsars of 500 TOAs (6
+// chunks of 16 tiles): 14.4 us a launch with one wave a chunk, 6.9 with eight;
+// with a continuous wave (33 chains) 20 and 12.8.  Beyond that line more waves
+// cost: 192 chunks of 67 pulsars at 64 chains take 13 us more with eight waves
+// than with the four they are tuned to.
+int toa_waves(const ptafs_dataset *ds) {
+  int w = ds->wpb;
+  while (w < 8 && 2 * w <= ds->max_chunk_tiles && w * ds->n_chunks < ds->base.n_cu) w *= 2;
+  return w;
 }
 
 // A captured trajectory graph holds the addresses of the chunk table, the
@@ -403,7 +422,7 @@ int enqueue_eval(ptafs_dataset *ds, int C, const double *x, double *logp, double
   if (plain) {
     for (int p = 0; p < D.n_psr; ++p) PT_TRY(ptk::launch_toa_plain_psr(D, p, ds->psr_nchunks[p], s));
   } else {
-    PT_TRY(ptk::launch_toa_mfma(D, ds->wpb, ds->xcd_map, s));
+    PT_TRY(ptk::launch_toa_mfma(D, toa_waves(ds), ds->xcd_map, s));
   }
   PT_TRY(ptk::launch_reduce_chunks(D, s));
   PT_TRY(ptk::launch_spectral_bwd(D, x, grad, s));
@@ -923,7 +942,7 @@ int ptafs_profile_stages(ptafs_dataset *ds, int32_t n_chains, const double *x, d
         e = ptk::launch_toa_plain_psr(D, p, ds->psr_nchunks[p], s);
       step(1, e);
     } else {
-      step(1, ptk::launch_toa_mfma(D, ds->wpb, ds->xcd_map, s));
+      step(1, ptk::launch_toa_mfma(D, toa_waves(ds), ds->xcd_map, s));
     }
     step(2, ptk::launch_reduce_chunks(D, s));
     {
