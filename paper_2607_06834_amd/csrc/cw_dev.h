@@ -43,28 +43,27 @@ enum CwRow {
 };
 static_assert(kCwRows <= kCwConst, "CW constant table too small");
 
-// Fill the constants of one chain for pulsar unit vector p.  th = the 8 CW
-// parameters; a null th (padding chain or rejected chain) gives zero delay.
-__device__ inline void cw_constants(const double *th, const double *p, double out[kCwRows]) {
-  for (int i = 0; i < kCwRows; ++i) out[i] = 0.0;
-  if (!th) return;
-  const double cth = th[0], phi = th[1];
-  const double M = exp(kLn10 * th[2]) * kTsun;
-  const double w0 = kPi * exp(kLn10 * th[3]);
+// The constants of one chain for pulsar unit vector p in two parts: those of the
+// orbit from the 8 CW parameters th and 10^th of the chirp mass, the frequency and
+// the strain, and those of the sky position and the polarisation from sin and cos
+// of 2 psi and of phi.
+__device__ inline void cw_orbit(const double *th, double m10, double f10, double h10, double *out) {
+  const double M = m10 * kTsun;
+  const double w0 = kPi * f10;
   const double X = exp((5.0 / 3.0) * log(M * w0));
   out[kCwK1] = 256.0 / 5.0 * X * w0;
   out[kCwInv32X] = 1.0 / (32.0 * X);
   out[kCwPhi0] = th[4];
-  out[kCwA0] = exp(kLn10 * th[7]) / (2.0 * w0);
+  out[kCwA0] = h10 / (2.0 * w0);
   out[kCwCi] = th[5];
-  double s2s, c2s;
-  sincos(2.0 * th[6], &s2s, &c2s);
+}
+
+__device__ inline void cw_sky(double cth, const double *p, double s2s, double c2s, double sph, double cph,
+                              double *out) {
   out[kCwC2s] = c2s;
   out[kCwS2s] = s2s;
   // antenna pattern and its derivatives in (cos theta, phi)
   const double sth = sqrt(1.0 - cth * cth);
-  double sph, cph;
-  sincos(phi, &sph, &cph);
   const double mp = sph * p[0] - cph * p[1];
   const double np = -cth * cph * p[0] - cth * sph * p[1] + sth * p[2];
   const double op = -(sth * cph * p[0] + sth * sph * p[1] + cth * p[2]);
@@ -90,6 +89,18 @@ __device__ inline void cw_constants(const double *th, const double *p, double ou
     out[kCwDfpP] = (mp * dmp - np * dnp) / den - fp * dop / den;
     out[kCwDfxP] = (dmp * np + mp * dnp) / den - fx * dop / den;
   }
+}
+
+// Fill the constants of one chain; a null th (padding chain or rejected chain)
+// gives zero delay.
+__device__ inline void cw_constants(const double *th, const double *p, double out[kCwRows]) {
+  for (int i = 0; i < kCwRows; ++i) out[i] = 0.0;
+  if (!th) return;
+  cw_orbit(th, exp(kLn10 * th[2]), exp(kLn10 * th[3]), exp(kLn10 * th[7]), out);
+  double s2s, c2s, sph, cph;
+  sincos(2.0 * th[6], &s2s, &c2s);
+  sincos(th[1], &sph, &cph);
+  cw_sky(th[0], p, s2s, c2s, sph, cph, out);
 }
 
 // sin and cos of x, |x| < 2^40 (a phase beyond has no digits left): x less the

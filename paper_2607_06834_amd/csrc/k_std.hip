@@ -605,188 +605,252 @@ __device__ inline pt::CwLane cw_lane(const double cst[pt::kCwRows]) {
   return L;
 }
 
-// The CW kernels take a pulsar and a block of kCwChains chains per workgroup,
-// so that every table entry (the transform, S_D, Q_D) is loaded once for the
-// block; thread t works on row t % 128 for the chains of half t / 128.
-constexpr int kCwChains = 16;
+// The CW kernels take a pulsar and a block of kCwChains = 16 chains per workgroup
+// of eight waves: each table (the transform, S_D, Q_D) is one operand of matrix
+// products with the chains as the other's 16 columns, a wave per 16 rows.
+// Vectors of the block lie in LDS as [row][16 chains], rows of kCwLd doubles
+// (lanes 16 apart read rows four apart: other halves of the banks), zero beyond
+// their length.  What bounds them: the 96 matrix instructions a wave, two
+// workgroups on more than half of the compute units at 100 pulsars x 64 chains
+// (11 us), and the waveform ahead of them; the tables are loaded a product ahead.
+// With a table row per thread and vector FMAs (eight LDS reads a table entry)
+// they took 53 and 50 us there, with four waves and the tables loaded where
+// they are used 32 and 35, now 27 and 29.
+constexpr int kCwChains = 16, kCwLd = 20, kCwRowsMax = 16 * ((ps::kMaxCwM + 15) / 16), kCwT = 512;
 
-// Constants of the block's chains for pulsar I (cst: kCwChains x kCwRows, LDS).
+// Constants of the block's chains for pulsar I (cst: kCwChains x kCwRows, LDS):
+// wave 0 the orbit, its three powers of ten in groups of 16 lanes, wave 1 the sky
+// position, its two sines likewise (a chain's constants in one lane are a serial
+// chain of about 4 us).
 __device__ inline void cw_block_constants(const StdDev &S, const double *x, int I, int c0, int nc,
                                           double *cst) {
-  const int tid = threadIdx.x;
-  if (tid < nc) pt::cw_constants(x + (size_t)(c0 + tid) * S.d + S.off_cw, S.cw_pos + 3 * I,
-                                 cst + tid * pt::kCwRows);
+  const int tid = threadIdx.x, l = tid & 63, ch = l & 15, g = l >> 4;
+  if (tid >= 128) return;
+  const double *th = x + (size_t)(c0 + min(ch, nc - 1)) * S.d + S.off_cw;
+  double *o = cst + ch * pt::kCwRows;
+  if (tid < 64) {
+    const double e = exp(pt::kLn10 * th[g == 0 ? 2 : g == 1 ? 3 : 7]);
+    const double f10 = __shfl(e, 16 + ch, 64), h10 = __shfl(e, 32 + ch, 64);
+    if (g == 0) pt::cw_orbit(th, e, f10, h10, o);
+  } else {
+    double sn, cs;
+    sincos(g == 0 ? 2.0 * th[6] : th[1], &sn, &cs);
+    const double sph = __shfl(sn, 16 + ch, 64), cph = __shfl(cs, 16 + ch, 64);
+    if (g == 0) pt::cw_sky(th[0], S.cw_pos + 3 * I, sn, cs, sph, cph, o);
+  }
+}
+
+// Four 16-column blocks of 16 rows of a table as operands of sixteen products:
+// lane (c, q) holds row r0 + c, columns 16 (b + u) + 4 q + i in a[4 u + i], so
+// that a row-major table (ks = 1) is read in runs of four.  Element (row, k) is
+// at row rs + k ks; rows past nr and columns past nk repeat the last, blocks
+// past nk are not read.
+struct TableRows {
+  const double *p;
+  int ks, nk, q;
+  __device__ __forceinline__ TableRows(const double *A, int rs, int ks_, int nr, int nk_, int r0, int c, int q_)
+      : p(A + (size_t)min(r0 + c, nr - 1) * rs), ks(ks_), nk(nk_), q(q_) {}
+};
+struct alignas(8) Run4 { double v[4]; };
+
+__device__ __forceinline__ void load_block(double *a, const TableRows &R, int b) {
+  const int k = 16 * b + 4 * R.q;
+  if (16 * b + 16 <= R.nk && R.ks == 1) {
+    const Run4 t = *reinterpret_cast<const Run4 *>(R.p + k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = t.v[i];
+  } else if (16 * b < R.nk) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = R.p[(size_t)min(k + i, R.nk - 1) * R.ks];
+  }
+}
+
+// acc += the block's columns times rows 16 b + 4 q + i of B ([k][kCwLd], LDS,
+// zero from nk to the block's end): result row r0 + q + 4 v of chain c in acc[v].
+__device__ __forceinline__ void mul_block(v4d &acc, const double *a, int nk, const double *B, int b, int c, int q) {
+  if (16 * b < nk) {
+    double y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y[i] = B[(16 * b + 4 * q + i) * kCwLd + c];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], y[i], acc, 0, 0, 0);
+  }
+}
+
+struct Half {   // four blocks
+  double a[16];
+  __device__ __forceinline__ void load(const TableRows &R, int b) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) load_block(a + 4 * u, R, b + u);
+  }
+  __device__ __forceinline__ void mul(v4d &acc, int nk, const double *B, int b, int c, int q) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) mul_block(acc, a + 4 * u, nk, B, b + u, c, q);
+  }
+};
+
+// The wave's 16 rows of (table) B; h0, h1 hold the table's blocks on entry and
+// those of `next` on return (up to 128 columns; the ninth block of a table of
+// 129 is read here).
+__device__ __forceinline__ v4d table_product(Half &h0, Half &h1, const TableRows &R, const double *B, int c,
+                                             const TableRows &next) {
+  v4d acc{0.0, 0.0, 0.0, 0.0};
+  h0.mul(acc, R.nk, B, 0, c, R.q);
+  h0.load(next, 0);
+  h1.mul(acc, R.nk, B, 4, c, R.q);
+  h1.load(next, 4);
+  if (R.nk > 128) {
+    double a[4];
+    load_block(a, R, 8);
+    mul_block(acc, a, R.nk, B, 8, c, R.q);
+  }
+  return acc;
 }
 
 // Forward: the delay at the md sample times t_j = j T_D / md, its transform a_D
 // (Eq. det_F_basis), then d_bar = d - S_D a_D (reversed order, zero-padded, as
 // k_std_fwd reads it) and c_bar = c - 2 e_D^T a_D + a_D^T Q_D a_D.
-__global__ __launch_bounds__(256) void k_std_cw_fwd(StdDev S, const double *__restrict__ x) {
-  constexpr int H = kCwChains / 2;
+__global__ __launch_bounds__(kCwT, 4) void k_std_cw_fwd(StdDev S, const double *__restrict__ x) {
   __shared__ double cst[kCwChains * pt::kCwRows];
-  __shared__ double hs[kCwChains][ps::kMaxCwM];
-  __shared__ double ad[kCwChains][ps::kMaxCw2];
-  __shared__ double cpart[2][kCwChains][4];
-  const int tid = threadIdx.x;
+  __shared__ double hs[kCwRowsMax * kCwLd];   // the delays, later S_D a_D
+  __shared__ double ad[kCwRowsMax * kCwLd];
+  __shared__ double cpart[kCwT / 64][kCwChains];
+  const int tid = threadIdx.x, w = tid >> 6, c = tid & 15, q = (tid & 63) >> 4;
   const int nb = (S.n_chains + kCwChains - 1) / kCwChains;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / nb, c0 = (pi - I * nb) * kCwChains;
   const int nc = min(kCwChains, S.n_chains - c0);
   const int K2 = 2 * S.kd, M = S.md, P = S.P, pp = S.pp;
+  const TableRows dft(S.cw_dft, M, 1, K2, M, 16 * w, c, q);
+  const TableRows sd(S.cw_sd + (size_t)I * P * K2, K2, 1, P, K2, 16 * w, c, q);
+  const TableRows qd(S.cw_qd + (size_t)I * K2 * K2, 1, K2, K2, K2, 16 * w, c, q);   // (symmetric)
   cw_block_constants(S, x, I, c0, nc, cst);
   __syncthreads();
-  for (int e = tid; e < kCwChains * M; e += 256) {
-    const int ch = e / M, j = e - ch * M;
-    hs[ch][j] = ch < nc ? cw_lane(cst + ch * pt::kCwRows).delay((double)j * S.td / M).h : 0.0;
-  }
-  __syncthreads();
-  const int row = tid & 127, h0 = (tid >> 7) * H;
-  // a_D
-  if (row < K2) {
-    double acc[H];
-#pragma unroll
-    for (int u = 0; u < H; ++u) acc[u] = 0.0;
-    const double *f = S.cw_dft + (size_t)row * M;
-    for (int j = 0; j < M; ++j) {
-      const double fv = f[j];
-#pragma unroll
-      for (int u = 0; u < H; ++u) acc[u] = fma(fv, hs[h0 + u][j], acc[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < H; ++u) {
-      ad[h0 + u][row] = acc[u];
-      if (h0 + u < nc) S.cw_ad[((size_t)(c0 + h0 + u) * S.n_psr + I) * K2 + row] = acc[u];
-    }
-  }
-  __syncthreads();
-  // d_bar, row = the reversed index r
-  if (row < pp) {
-    double acc[H];
-#pragma unroll
-    for (int u = 0; u < H; ++u) acc[u] = 0.0;
-    if (row < P) {
-      const double *sd = S.cw_sd + ((size_t)I * P + (P - 1 - row)) * K2;
-      for (int k = 0; k < K2; ++k) {
-        const double sv = sd[k];
-#pragma unroll
-        for (int u = 0; u < H; ++u) acc[u] = fma(sv, ad[h0 + u][k], acc[u]);
-      }
-    }
-    const double dv = row < P ? S.dvec[(size_t)I * pp + row] : 0.0;
-#pragma unroll
-    for (int u = 0; u < H; ++u)
-      if (h0 + u < nc) S.dbar[((size_t)(c0 + h0 + u) * S.n_psr + I) * pp + row] = row < P ? dv - acc[u] : 0.0;
-  }
-  // c_bar: a_D^T (Q_D a_D - 2 e_D) per chain, summed over the rows of each wave
   {
-    double part[H];
+    const pt::CwLane L = cw_lane(cst + c * pt::kCwRows);
+    for (int j = tid >> 4; j < kCwRowsMax; j += kCwT / 16)
+      hs[j * kCwLd + c] = (c < nc && j < M) ? L.delay((double)j * S.td / M).h : 0.0;
+  }
+  Half h0, h1;
+  h0.load(dft, 0);
+  h1.load(dft, 4);
+  __syncthreads();
+  const v4d a = table_product(h0, h1, dft, hs, c, sd);   // a_D
 #pragma unroll
-    for (int u = 0; u < H; ++u) part[u] = 0.0;
-    if (row < K2) {
-      double acc[H];
-#pragma unroll
-      for (int u = 0; u < H; ++u) acc[u] = 0.0;
-      const double *qd = S.cw_qd + (size_t)I * K2 * K2 + row;   // Q_D is symmetric: column row
-      for (int k = 0; k < K2; ++k) {
-        const double qv = qd[(size_t)k * K2];
-#pragma unroll
-        for (int u = 0; u < H; ++u) acc[u] = fma(qv, ad[h0 + u][k], acc[u]);
-      }
-      const double ev = S.cw_ed[(size_t)I * K2 + row];
-#pragma unroll
-      for (int u = 0; u < H; ++u) part[u] = ad[h0 + u][row] * (acc[u] - 2.0 * ev);
+  for (int v = 0; v < 4; ++v) {
+    const int r = 16 * w + q + 4 * v;
+    ad[r * kCwLd + c] = r < K2 ? a[v] : 0.0;
+  }
+  __syncthreads();
+  for (int e = tid; e < nc * K2; e += kCwT) {
+    const int ch = e / K2, k = e - ch * K2;
+    S.cw_ad[((size_t)(c0 + ch) * S.n_psr + I) * K2 + k] = ad[k * kCwLd + ch];
+  }
+  // S_D a_D, and a_D^T (Q_D a_D - 2 e_D) per chain
+  {
+    v4d s{0.0, 0.0, 0.0, 0.0};
+    if (16 * w < P) {
+      s = table_product(h0, h1, sd, ad, c, qd);
+    } else {
+      h0.load(qd, 0);
+      h1.load(qd, 4);
     }
+    v4d qa{0.0, 0.0, 0.0, 0.0};
+    h0.mul(qa, K2, ad, 0, c, q);
+    h1.mul(qa, K2, ad, 4, c, q);
+    double part = 0.0;
 #pragma unroll
-    for (int u = 0; u < H; ++u) {
-      double v = part[u];
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * w + q + 4 * v;
+      hs[r * kCwLd + c] = s[v];
+      if (r < K2) part += a[v] * (qa[v] - 2.0 * S.cw_ed[(size_t)I * K2 + r]);
+    }
+    part = ln::row_sum_d(part);
+    if (q == 0) cpart[w][c] = part;
+  }
+  __syncthreads();
+  for (int e = tid; e < nc * pp; e += kCwT) {
+    const int ch = e / pp, r = e - ch * pp;
+    S.dbar[((size_t)(c0 + ch) * S.n_psr + I) * pp + r] =
+        r < P ? S.dvec[(size_t)I * pp + r] - hs[(P - 1 - r) * kCwLd + ch] : 0.0;
+  }
+  if (tid < nc) {
+    double cb = 0.0;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if ((tid & 63) == 0) cpart[tid >> 7][h0 + u][(tid >> 6) & 1] = v;
-    }
-    __syncthreads();
-    if (tid < nc) {
-      const int hh = tid / H;
-      const double v = cpart[hh][tid][0] + cpart[hh][tid][1];
-      S.cbar[(size_t)(c0 + tid) * S.n_psr + I] = S.cconst[2 * I] + v;
-    }
+    for (int u = 0; u < kCwT / 64; ++u) cb += cpart[u][tid];
+    S.cbar[(size_t)(c0 + tid) * S.n_psr + I] = S.cconst[2 * I] + cb;
   }
 }
 
 // dlog p / d a_D = -S_D^T g + beta (e_D - Q_D a_D) with g = dlog p / d d_bar
 // (k_std_bwd), then g_h = (transform)^T dlog p / d a_D at the sample times and
 // the pulsar's part of dlog p / d theta_cw = sum_j g_h,j dh_j / d theta.
-__global__ __launch_bounds__(256) void k_std_cw_bwd(StdDev S, const double *__restrict__ x) {
-  constexpr int H = kCwChains / 2;
+__global__ __launch_bounds__(kCwT, 4) void k_std_cw_bwd(StdDev S, const double *__restrict__ x) {
   __shared__ double cst[kCwChains * pt::kCwRows];
-  __shared__ double gb[kCwChains][ps::kMaxCwM];   // dlog p / d d_bar, later g_h
-  __shared__ double ad[kCwChains][ps::kMaxCw2];
-  __shared__ double ga[kCwChains][ps::kMaxCw2];
-  const int tid = threadIdx.x;
+  __shared__ double gb[kCwRowsMax * kCwLd];   // dlog p / d d_bar, later g_h
+  __shared__ double ad[kCwRowsMax * kCwLd];   // a_D, later dlog p / d a_D
+  const int tid = threadIdx.x, w = tid >> 6, c = tid & 15, q = (tid & 63) >> 4;
   const int nb = (S.n_chains + kCwChains - 1) / kCwChains;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / nb, c0 = (pi - I * nb) * kCwChains;
   const int nc = min(kCwChains, S.n_chains - c0);
   const int K2 = 2 * S.kd, M = S.md, P = S.P;
+  const TableRows sdt(S.cw_sd + (size_t)I * P * K2, 1, K2, K2, P, 16 * w, c, q);
+  const TableRows qd(S.cw_qd + (size_t)I * K2 * K2, 1, K2, K2, K2, 16 * w, c, q);
+  const TableRows dft(S.cw_dft, 1, M, M, K2, 16 * w, c, q);
+  Half h0, h1;
+  h0.load(sdt, 0);
+  h1.load(sdt, 4);
   cw_block_constants(S, x, I, c0, nc, cst);
-  for (int e = tid; e < kCwChains * P; e += 256) {
-    const int ch = e / P, j = e - ch * P;
-    gb[ch][j] = ch < nc ? S.gdbar[((size_t)(c0 + ch) * S.n_psr + I) * P + j] : 0.0;
-  }
-  for (int e = tid; e < kCwChains * K2; e += 256) {
-    const int ch = e / K2, k = e - ch * K2;
-    ad[ch][k] = ch < nc ? S.cw_ad[((size_t)(c0 + ch) * S.n_psr + I) * K2 + k] : 0.0;
+  for (int e = tid; e < kCwChains * kCwRowsMax; e += kCwT) {
+    const int ch = e / kCwRowsMax, j = e - ch * kCwRowsMax;
+    const size_t ci = (size_t)(c0 + (ch < nc ? ch : 0)) * S.n_psr + I;
+    gb[j * kCwLd + ch] = (ch < nc && j < P) ? S.gdbar[ci * P + j] : 0.0;
+    ad[j * kCwLd + ch] = (ch < nc && j < K2) ? S.cw_ad[ci * K2 + j] : 0.0;
   }
   __syncthreads();
-  const int row = tid & 127, h0 = (tid >> 7) * H;
-  if (row < K2) {
-    double s1[H], s2[H];
-#pragma unroll
-    for (int u = 0; u < H; ++u) s1[u] = s2[u] = 0.0;
-    const double *sd = S.cw_sd + (size_t)I * P * K2 + row;
-    for (int j = 0; j < P; ++j) {
-      const double sv = sd[(size_t)j * K2];
-#pragma unroll
-      for (int u = 0; u < H; ++u) s1[u] = fma(sv, gb[h0 + u][j], s1[u]);
-    }
-    const double *qd = S.cw_qd + (size_t)I * K2 * K2 + row;   // Q_D is symmetric: column row
-    for (int k = 0; k < K2; ++k) {
-      const double qv = qd[(size_t)k * K2];
-#pragma unroll
-      for (int u = 0; u < H; ++u) s2[u] = fma(qv, ad[h0 + u][k], s2[u]);
-    }
-    const double ev = S.cw_ed[(size_t)I * K2 + row];
-#pragma unroll
-    for (int u = 0; u < H; ++u) {
-      const int ch = h0 + u;
-      const double beta = (ch < nc && S.beta) ? S.beta[c0 + ch] : 1.0;
-      ga[ch][row] = beta * (ev - s2[u]) - s1[u];
-    }
-  }
-  __syncthreads();
-  // g_h at the sample times (up to 129 of them: rows 0..127, then 128)
-  for (int j = row; j < M; j += 128) {
-    double acc[H];
-#pragma unroll
-    for (int u = 0; u < H; ++u) acc[u] = 0.0;
-    for (int k = 0; k < K2; ++k) {
-      const double fv = S.cw_dft[(size_t)k * M + j];
-#pragma unroll
-      for (int u = 0; u < H; ++u) acc[u] = fma(fv, ga[h0 + u][k], acc[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < H; ++u) gb[h0 + u][j] = acc[u];
-  }
-  __syncthreads();
-  // the waveform's derivative: chain tid / 16, samples tid % 16 + 16 i, then
-  // the 16 lanes of the chain summed in order
   {
-    const int ch = tid >> 4, l16 = tid & 15;
+    const v4d s1 = table_product(h0, h1, sdt, gb, c, qd);
+    const v4d s2 = table_product(h0, h1, qd, ad, c, dft);
+    __syncthreads();
+    const double beta = (c < nc && S.beta) ? S.beta[c0 + c] : 1.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = 16 * w + q + 4 * v;
+      ad[r * kCwLd + c] = r < K2 ? beta * (S.cw_ed[(size_t)I * K2 + r] - s2[v]) - s1[v] : 0.0;
+    }
+  }
+  __syncthreads();
+  // g_h at the sample times (the 129th in a tile of its own)
+  {
+    v4d gh{0.0, 0.0, 0.0, 0.0};
+    h0.mul(gh, K2, ad, 0, c, q);
+    h1.mul(gh, K2, ad, 4, c, q);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gb[(16 * w + q + 4 * v) * kCwLd + c] = gh[v];
+    if (M > 128 && w == 0) {
+      const TableRows last(S.cw_dft, 1, M, M, K2, 128, c, q);
+      h0.load(last, 0);
+      h1.load(last, 4);
+      gh = v4d{0.0, 0.0, 0.0, 0.0};
+      h0.mul(gh, K2, ad, 0, c, q);
+      h1.mul(gh, K2, ad, 4, c, q);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) gb[(128 + q + 4 * v) * kCwLd + c] = gh[v];
+    }
+  }
+  __syncthreads();
+  // the waveform's derivative: chain tid / 32, samples tid % 32 + 32 i, then
+  // the 32 lanes of the chain summed in order
+  {
+    constexpr int LC = kCwT / kCwChains;
+    const int ch = tid / LC, lc = tid % LC;
     double out[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (ch < nc) {
       const double *cc = cst + ch * pt::kCwRows;
       const pt::CwLane L = cw_lane(cc);
       double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      for (int j = l16; j < M; j += 16) L.adjoint(L.delay((double)j * S.td / M), gb[ch][j], acc);
+      for (int j = lc; j < M; j += LC) L.adjoint(L.delay((double)j * S.td / M), gb[j * kCwLd + ch], acc);
       // the sky pair through the antenna derivatives, ln 10 for the log10 parameters
       out[0] = -(cc[pt::kCwDfpC] * acc[0] + cc[pt::kCwDfxC] * acc[1]);
       out[1] = -(cc[pt::kCwDfpP] * acc[0] + cc[pt::kCwDfxP] * acc[1]);
@@ -801,10 +865,10 @@ __global__ __launch_bounds__(256) void k_std_cw_bwd(StdDev S, const double *__re
     for (int v = 0; v < 8; ++v) {
       double t = out[v];
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+      for (int o = LC / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
       out[v] = t;
     }
-    if (ch < nc && l16 == 0) {
+    if (ch < nc && lc == 0) {
       double *o = S.dcw + ((size_t)(c0 + ch) * S.n_psr + I) * 8;
 #pragma unroll
       for (int v = 0; v < 8; ++v) o[v] = out[v];
@@ -1239,56 +1303,124 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_split_f
   }
 }
 
-// Per (pulsar, chain): a_G, a_R and a from the combined MAP (avec, written by
-// k_std_fwd with z = 0) and the sets' L_b z_b; v1 = beta (d - S0 a) and
+// Per (pulsar, block of 16 chains): a_G, a_R and a from the combined MAP (avec,
+// written by k_std_fwd with z = 0) and the sets' L_b z_b; v1 = beta (d - S0 a) and
 // beta log L(a) with S0 a formed directly (a is no longer a_hat + L z of one
-// factorisation); the Jacobian ln det L_G + ln det L_R.
-__global__ __launch_bounds__(256) void k_split_comb(StdDev S, const double *__restrict__ x) {
-  __shared__ double av[16 * ps::kMaxTiles];
-  __shared__ double red[12];
-  const int tid = threadIdx.x;
+// factorisation), one matrix product for the block (S0 is read once for 16
+// chains); the Jacobian ln det L_G + ln det L_R.  Eight waves, the rows of one
+// tile each; thread tid takes row tid % 128 of the chains tid / 128, tid / 128 + 4,
+// ... where vectors are read or written, and loads all of them before the first
+// is used (with the loads inside the branches of the sets 32 us at 67 pulsars x
+// 64 chains, with sixteen waves and two rounds of workgroups 38).
+// What bounds it: the vectors (28 MB, 6 us there) and the chain from the prior
+// variances to the stores.  Per (pulsar, chain) with S0 read for each it took
+// 65 us (7.6 TB/s from L2), now 24.
+constexpr int kCombT = 512;
+
+// Spectrum of one process at frequency k from its parameters a (and b).
+struct SpecIn { double a, b; };
+__device__ __forceinline__ SpecIn spec_load(const StdDev &S, const double *xc, int off, int k, bool in) {
+  const int o = !in ? 0 : S.free_spec ? off + k : off;
+  return {xc[o], S.free_spec ? 0.0 : xc[o + 1]};
+}
+__device__ __forceinline__ double spec_eval(const StdDev &S, SpecIn p, double lnfy, bool in) {
+  const double e = S.free_spec ? ps::kLn10 * p.a : 2.0 * ps::kLn10 * p.a - p.b * lnfy + S.pl_c;
+  return in ? exp(e) : 0.0;
+}
+
+__global__ __launch_bounds__(kCombT, 4) void k_split_comb(StdDev S, const double *__restrict__ x) {
+  constexpr int NR = 16 * ps::kMaxTiles, G = kCombT / NR, NC = kCwChains / G;
+  __shared__ double av[NR * kCwLd];   // a, reversed order, later S0~ a~
+  __shared__ double red[kCombT / 64][NC][2];
+  const int tid = threadIdx.x, w = tid >> 6;
+  const int nb = (S.n_chains + kCwChains - 1) / kCwChains;
   const int pi = xcd_index(blockIdx.x, gridDim.x);
-  const int I = pi / S.n_chains, c = pi - I * S.n_chains;
-  const double *xc = x + (size_t)c * S.d;
-  const double beta = S.beta ? S.beta[c] : 1.0;
-  const int P = S.P, pp = S.pp, j = tid;
-  const size_t ci = (size_t)c * S.n_psr + I, vb = ci * pp;
-  double a = 0.0, d = 0.0;
-  if (j < P) {
-    const double ah = S.avec[vb + j];
-    const double id = 1.0 / ps::curn_var(S, xc, I, j);
-    if (j < S.PG) {
-      const double g = ps::spec_value(S, xc, 0, I, j >> 1) * id * ah + S.lzg[ci * S.ppg + j];
-      S.ag[ci * S.ppg + j] = g;
-      a += g;
+  const int I = pi / nb, c0 = (pi - I * nb) * kCwChains;
+  const int nc = min(kCwChains, S.n_chains - c0);
+  const int P = S.P, pp = S.pp, j = tid & (NR - 1), g0 = tid / NR;
+  const int c16 = tid & 15, q = (tid & 63) >> 4;
+  double a[NC], d[NC];
+  {
+    // row j: the sets it is in, its frequency there, and the set's row (rows past
+    // P and chains past nc read the last and write nothing)
+    const int jj = min(j, P - 1);
+    const bool dm = jj >= 2 * S.ka, in_g = jj < S.PG, in_r = dm || jj < 2 * S.nf_rn;
+    const int k = (dm ? jj - 2 * S.ka : jj) >> 1, jr = dm ? jj - 2 * S.ka + 2 * S.nf_rn : jj;
+    const int off_r = dm ? S.off_dm + I * S.w_dm : S.off_rn + I * S.w_rn;
+    const double lnfy = S.lnfy[k];
+    double ah[NC], lg[NC], lr[NC];
+    SpecIn pg[NC], pr[NC];
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      const int c = c0 + min(g0 + G * u, nc - 1);
+      const double *xc = x + (size_t)c * S.d;
+      const size_t ci = (size_t)c * S.n_psr + I, vb = ci * pp;
+      pg[u] = spec_load(S, xc, S.off_gw, k, in_g);
+      pr[u] = spec_load(S, xc, off_r, k, in_r);
+      ah[u] = S.avec[vb + jj];
+      lg[u] = S.PG ? S.lzg[ci * S.ppg + (in_g ? jj : 0)] : 0.0;
+      lr[u] = S.PR ? S.lzr[ci * S.ppr + (in_r ? jr : 0)] : 0.0;
+      d[u] = (S.has_cw ? S.dbar + vb : S.dvec + (size_t)I * pp)[P - 1 - jj];
     }
-    if (j < 2 * S.nf_rn || j >= 2 * S.ka) {
-      const int jr = j < 2 * S.nf_rn ? j : j - 2 * S.ka + 2 * S.nf_rn;
-      const double g = ps::split_var(S, xc, I, 1, jr) * id * ah + S.lzr[ci * S.ppr + jr];
-      S.ar[ci * S.ppr + jr] = g;
-      a += g;
+#pragma unroll
+    for (int u = 0; u < NC; ++u) {
+      const int ch = g0 + G * u;
+      const size_t ci = (size_t)(c0 + ch) * S.n_psr + I;
+      const double vg = spec_eval(S, pg[u], lnfy, in_g), vr = spec_eval(S, pr[u], lnfy, in_r);
+      const double id = 1.0 / (vg + vr);
+      const bool on = ch < nc && j < P;
+      const double g = in_g ? vg * id * ah[u] + lg[u] : 0.0, r = in_r ? vr * id * ah[u] + lr[u] : 0.0;
+      if (on && in_g) S.ag[ci * S.ppg + j] = g;
+      if (on && in_r) S.ar[ci * S.ppr + jr] = r;
+      a[u] = on ? g + r : 0.0;
+      av[(j < P ? P - 1 - j : j) * kCwLd + ch] = a[u];
     }
-    av[j] = a;
-    d = (S.has_cw ? S.dbar + vb : S.dvec + (size_t)I * pp)[P - 1 - j];
+  }
+  const TableRows s0(S.s0 + (size_t)I * pp * pp, pp, 1, pp, pp, 16 * w, c16, q);
+  Half h0, h1;
+  h0.load(s0, 0);
+  h1.load(s0, 4);
+  __syncthreads();
+  v4d acc{0.0, 0.0, 0.0, 0.0};
+  h0.mul(acc, pp, av, 0, c16, q);
+  h1.mul(acc, pp, av, 4, c16, q);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) av[(16 * w + q + 4 * v) * kCwLd + c16] = acc[v];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < NC; ++u) {
+    const int ch = g0 + G * u, c = c0 + ch;
+    double pd = 0.0, pq = 0.0;
+    if (ch < nc && j < P) {
+      const double beta = S.beta ? S.beta[c] : 1.0;
+      const size_t vb = ((size_t)c * S.n_psr + I) * pp;
+      const double s = av[(P - 1 - j) * kCwLd + ch];
+      S.avec[vb + j] = a[u];
+      S.v1[vb + (P - 1 - j)] = beta * (d[u] - s);
+      pd = a[u] * d[u];
+      pq = a[u] * s;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      pd += __shfl_xor(pd, o, 64);
+      pq += __shfl_xor(pq, o, 64);
+    }
+    if ((tid & 63) == 0) {
+      red[w][u][0] = pd;
+      red[w][u][1] = pq;
+    }
   }
   __syncthreads();
-  double part_d = 0.0, part_q = 0.0, part_n = 0.0;
-  if (j < P) {
-    // (S0 a)_j down column P - 1 - j of the symmetric S0~ (coalesced over j)
-    const double *s0 = S.s0 + (size_t)I * pp * pp + (P - 1 - j);
-    double s = 0.0;
-    for (int m = 0; m < P; ++m) s = fma(s0[(size_t)(P - 1 - m) * pp], av[m], s);
-    S.avec[vb + j] = a;
-    S.v1[vb + (P - 1 - j)] = beta * (d - s);
-    part_d = a * d;
-    part_q = a * s;
-  }
-  block_sum3(part_d, part_q, part_n, red);
-  if (tid == 0) {
+  if (tid < nc) {
+    const int u = tid / G, w0 = 2 * (tid % G), c = c0 + tid;   // chain tid in the waves w0, w0 + 1
+    const double sd = red[w0][u][0] + red[w0 + 1][u][0], sq = red[w0][u][1] + red[w0 + 1][u][1];
+    const double beta = S.beta ? S.beta[c] : 1.0;
+    const size_t ci = (size_t)c * S.n_psr + I;
     const double *k2 = S.cconst + 2 * I;
-    const double c0 = S.has_cw ? S.cbar[ci] : k2[0];
+    const double cc = S.has_cw ? S.cbar[ci] : k2[0];
     double *o = S.lik + ci * 2;
-    o[0] = beta * ((k2[1] - 0.5 * c0) + (part_d - 0.5 * part_q));
+    o[0] = beta * ((k2[1] - 0.5 * cc) + (sd - 0.5 * sq));
     o[1] = S.jac_s[ci * 2] + S.jac_s[ci * 2 + 1];
   }
 }
@@ -1461,14 +1593,14 @@ namespace psk {
 hipError_t launch_std_cw_fwd(const StdDev &S, const double *x, hipStream_t s) {
   const int grid = ((S.n_chains + kCwChains - 1) / kCwChains) * S.n_psr;
   if (grid == 0 || !S.has_cw) return hipSuccess;
-  hipLaunchKernelGGL(k_std_cw_fwd, dim3(grid), dim3(256), 0, s, S, x);
+  hipLaunchKernelGGL(k_std_cw_fwd, dim3(grid), dim3(kCwT), 0, s, S, x);
   return hipGetLastError();
 }
 
 hipError_t launch_std_cw_bwd(const StdDev &S, const double *x, hipStream_t s) {
   const int grid = ((S.n_chains + kCwChains - 1) / kCwChains) * S.n_psr;
   if (grid == 0 || !S.has_cw) return hipSuccess;
-  hipLaunchKernelGGL(k_std_cw_bwd, dim3(grid), dim3(256), 0, s, S, x);
+  hipLaunchKernelGGL(k_std_cw_bwd, dim3(grid), dim3(kCwT), 0, s, S, x);
   return hipGetLastError();
 }
 
@@ -1507,7 +1639,7 @@ hipError_t launch_split_fwd(const StdDev &S, const double *x, hipStream_t s) {
   if (grid == 0 || !S.split) return hipSuccess;
   PS_DISPATCH(S.tpg, k_split_fac, ELIM_WAVES, grid, S, x, 0);
   PS_DISPATCH(S.tpr, k_split_fac, ELIM_WAVES, grid, S, x, 1);
-  hipLaunchKernelGGL(k_split_comb, dim3(grid), dim3(256), 0, s, S, x);
+  hipLaunchKernelGGL(k_split_comb, dim3(((S.n_chains + kCwChains - 1) / kCwChains) * S.n_psr), dim3(kCombT), 0, s, S, x);
   return hipGetLastError();
 }
 
