@@ -17,7 +17,7 @@
 // What bounds them: the chain of one problem (16 chains x 30 frequencies are
 // 480 problems for 256 compute units), in the forward the eight diagonal tiles
 // one after the other.  Per launch at 120 pulsars, 16 chains and 30 frequencies:
-// forward 47 us, adjoint 45.  A thread per row of L took 411 us, a thread per
+// forward 40 us, adjoint 45.  A thread per row of L took 411 us, a thread per
 // column of C^-1 (rows of C as scalar loads) 373, each with a launch for the
 // diagonal frequencies (9 and 6 us) beside it; one wave per problem, at 110
 // pulsars, 84 and 68.
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_fwd(Dev D, const double *_
   __shared__ int fail;
   const int prob = blockIdx.x;
   const int k0 = prob % D.nf_gw, c = prob / D.nf_gw;
-  const int tid = threadIdx.x;
+  const int tid = el::placed_tid<kW>();
   const int n = D.n_psr;
   const size_t cp = D.c_pad;
   const int rs = pt::harm_row(k0 + 1, 0), rc = pt::harm_row(k0 + 1, 1);
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_fwd(Dev D, const double *_
   // rows of block C and columns of block I), the row's spectrum and z, the box
 #pragma unroll
   for (int s = 0; s < E::NS; ++s) {
-    const double *g = D.gam_tile + (el.has(s) ? s * kW + el.w : 0) * 256 + el.lane;
+    const double *g = D.gam_tile + (el.has(s) ? tix(el.tile_i(s), el.tile_c(s)) : 0) * 256 + el.lane;
 #pragma unroll
     for (int v = 0; v < 4; ++v) el.a[s][v] = g[64 * v];
   }

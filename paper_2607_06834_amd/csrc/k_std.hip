@@ -51,17 +51,16 @@ using ps::StdDev;
 using ln::v4d;
 
 // Waves per (pulsar, chain) or (frequency, chain) elimination of T tiles, and the
-// waves a SIMD that its registers are held to.  A wave takes at most 15 tiles
-// (120 of its registers); more waves shorten a step and cost barriers and issue.
-// Measured for 1600 problems, us: T = 6 with 2 waves 83, with 3 76; T = 7 with 2
-// waves 115, 3 104, 4 106 (its first wave's chain 33 and 28); T = 5 for 4288
-// problems, 1 wave 95 and 2 waves 105; T = 4 for 6400, 1 wave 75, 2 waves 91;
-// T = 8 for 4288, 3 waves at four problems a compute unit 346, 4 waves at three
-// 310, at four (with register spills) 390.
+// waves a SIMD that its registers are held to.  One wave takes at most 15 tiles
+// (120 of its registers); from T = 6 three waves share them and a fourth takes the
+// diagonal tiles.  Measured, us: T = 5 for 4288 problems, 1 wave 95 and 2 waves
+// 105; T = 4 for 6400, 1 wave 75, 2 waves 91; T = 7 for 900, at three waves a SIMD
+// 102, at four (six registers spilled outside of the steps) 88; T = 8 for 4288, at
+// three 254, at four 296 (142 registers spilled).
 template <int T>
-constexpr int elim_waves() { return T <= 5 ? 1 : T == 6 ? 3 : 4; }
+constexpr int elim_waves() { return T <= 5 ? 1 : 4; }
 template <int T>
-constexpr int elim_occ() { return T <= 2 ? 4 : T == 5 ? 2 : 3; }
+constexpr int elim_occ() { return T <= 2 || T == 6 || T == 7 ? 4 : T == 5 ? 2 : 3; }
 
 // the plain row-major tile t of global memory as an MFMA B operand
 __device__ inline v4d ldg_cm(const double *t, int c, int q) {
@@ -126,17 +125,59 @@ __device__ inline void block_sum3(double &a, double &b, double &c, double *red) 
   c = (red[8] + red[9]) + (red[10] + red[11]);
 }
 
+// sum over a wave
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// The slots of a wave that holds tiles from S0~ (rows of block C, columns of
+// block I, every load issued before any use), and -(beta S0~ + diag(1 / D~)) of
+// them.  In a wave that waits for another's matrix instructions an FP64 operation
+// costs up to 64 cycles: the sign is changed without one, and beta = 1 takes none.
+template <int T, class E>
+__device__ __forceinline__ void load_gram(E &el, const double *__restrict__ s0) {
+  constexpr int pp = 16 * T;
+  if (!el.holds()) return;
+  const unsigned l = el.q * pp + el.c;
+#pragma unroll
+  for (int s = 0; s < E::NS; ++s) {
+    const double *t = s0 + (el.has(s) ? 16 * (el.tile_c(s) * pp + el.tile_i(s)) : 0);   // (the same in all lanes)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) el.a[s][v] = t[l + 4 * v * pp];
+  }
+}
+template <int T, class E>
+__device__ __forceinline__ void gram_slots(E &el, double beta, const double *di) {
+  if (!el.holds()) return;
+  if (beta != 1.0) {
+#pragma unroll
+    for (int s = 0; s < E::NS; ++s) el.a[s] *= beta;
+  }
+#pragma unroll
+  for (int s = 0; s < E::NS; ++s) {
+    el.a[s] = el::neg(el.a[s]);
+    if (el.tile_i(s) == el.tile_c(s)) {
+      const double d = di[16 * el.tile_i(s) + el.c];
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (el.q + 4 * v == el.c) el.a[s][v] -= d;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Forward per (pulsar, chain): transform, likelihood, Jacobian.
 // ---------------------------------------------------------------------------
 template <int T>
 __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd(StdDev S, const double *__restrict__ x) {
-  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  constexpr int W = elim_waves<T>(), pp = 16 * T;
   using E = el::Elim<T, W>;
   __shared__ el::Lds<T, W> L;
-  __shared__ double bv[2 * pp], tv[2 * pp], vdi[pp], red[W];   // (b, L z), (t, z), 1 / D~
+  __shared__ double bv[2 * pp], tv[2 * pp], vdi[pp], dv[W > 1 ? pp : 1];   // (b, L z), (t, z), 1 / D~, d
   __shared__ int flag;
-  const int tid = threadIdx.x;
+  const int tid = el::placed_tid<W>();
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
@@ -144,58 +185,56 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
   const int P = S.P;
   const size_t ci = (size_t)c * S.n_psr + I;
   E el(tid);
-  // A~ = beta S0~ + diag(1 / D~): S0~ into the slots (rows of block C, columns
-  // of block I), every load issued before any use
-  const double *s0 = S.s0 + (size_t)I * pp * pp + el.q * pp + el.c;
-#pragma unroll
-  for (int s = 0; s < E::NS; ++s) {
-    const int o = el.has(s) ? 16 * (el.tile_c(s) * pp + el.tile_i(s)) : 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) el.a[s][v] = s0[o + 4 * v * pp];
-  }
-  int bad = 0;
-  // d of the data, or of the data minus the deterministic signal
+  // A~ = beta S0~ + diag(1 / D~)
+  load_gram<T>(el, S.s0 + (size_t)I * pp * pp);
+  // d of the data, or of the data minus the deterministic signal; vectors in the
+  // wave that holds no tiles
   const double *dsrc = S.has_cw ? S.dbar + ci * pp : S.dvec + (size_t)I * pp;
-  for (int r = tid; r < pp; r += NTH) {
-    bv[2 * r] = (r < P) ? beta * dsrc[r] : 0.0;
-    bv[2 * r + 1] = 0.0;
-    // with split coefficients this is the combined MAP only (z = 0)
-    tv[2 * r + 1] = (r < P && !S.split) ? xc[S.off_z + I * P + (P - 1 - r)] : 0.0;
-    // a CURN variance that is not positive and finite leaves phi_CURN not
-    // positive definite
-    double di = 1.0;
-    if (r < P) {
-      const double Dv = ps::curn_var(S, xc, I, P - 1 - r);
-      if (!(Dv > 0.0 && isfinite(Dv))) bad = 1;
-      di = 1.0 / Dv;
-    }
-    vdi[r] = di;
-  }
-  bad = __syncthreads_or(bad);
-  if (tid == 0) flag = bad ? 0 : 1;
+  const int vt = E::vec_tid(tid);
+  if (vt >= 0) {
+    bool bad = false;
 #pragma unroll
-  for (int s = 0; s < E::NS; ++s) {
-    el.a[s] *= -beta;
-    if (el.tile_i(s) == el.tile_c(s)) {
-      const double di = vdi[16 * el.tile_i(s) + el.c];
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (el.q + 4 * v == el.c) el.a[s][v] -= di;
+    for (int u = 0; u < (pp + 63) / 64; ++u) {
+      const int r = vt + 64 * u;
+      if (r >= pp) break;
+      const double d = (r < P) ? dsrc[r] : 0.0;
+      if (W > 1) dv[r] = d;
+      bv[2 * r] = beta * d;
+      bv[2 * r + 1] = 0.0;
+      // with split coefficients this is the combined MAP only (z = 0)
+      tv[2 * r + 1] = (r < P && !S.split) ? xc[S.off_z + I * P + (P - 1 - r)] : 0.0;
+      if (r >= P) vdi[r] = 1.0;
     }
+    // a CURN variance that is not positive and finite leaves phi_CURN not positive
+    // definite; a lane per frequency, for the sine and the cosine row
+    static_assert(pp <= 128, "a lane per frequency");
+    if (2 * vt < P) {
+      const double Dv = ps::curn_var(S, xc, I, 2 * vt);
+      bad = !(Dv > 0.0 && isfinite(Dv));
+      const double di = 1.0 / Dv;
+      vdi[P - 1 - 2 * vt] = di;
+      vdi[P - 2 - 2 * vt] = di;
+    }
+    bad = __any(bad);
+    if (vt == 0) flag = bad ? 0 : 1;
   }
+  __syncthreads();
+  gram_slots<T>(el, beta, vdi);
   __syncthreads();
   // X = L~^-1, t = X beta d~ and L~ z~
   el.template run<1, 1>(L, &flag, bv, tv, [](int) {});
-  for (int r = tid; r < pp; r += NTH) tv[2 * r + 1] += tv[2 * r];
+  if (vt >= 0)
+    for (int r = vt; r < pp; r += 64) tv[2 * r + 1] += tv[2 * r];
   __syncthreads();
   // a_hat~ = X^T t, a~ = X^T (t + z~)
   double *part = L.row;
   static_assert(E::NT * 32 <= T * el::kTile, "the partial sums fit the row buffer");
   el.xty(part, tv);
-  el::store_x(el, S.xinv + ci * (E::NT * 256));
   __syncthreads();
+  el::store_x(el, S.xinv + ci * (E::NT * 256));
+  if (vt < 0) return;
   double part_d = 0.0, part_v = 0.0, part_j = 0.0;
-  for (int r = tid; r < pp; r += NTH) {
+  for (int r = vt; r < pp; r += 64) {
     const double sh = el::xty_sum<T, 2>(part, 0, r), sa = el::xty_sum<T, 2>(part, 1, r);
     S.ahat[ci * pp + r] = sh;
     // beta (d - S0 a) in the reversed order: A~ a~ = L~ (t + z~) = beta d~ + L~ z~,
@@ -204,15 +243,15 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
     S.v1[ci * pp + r] = v1;
     if (r < P) {
       S.avec[ci * pp + (P - 1 - r)] = sa;
-      part_d += sa * dsrc[r];
+      part_d += sa * (W > 1 ? dv[r] : dsrc[r]);
       part_j += log(L.rs[r]);
     }
     part_v += sa * v1;
   }
-  part_d = wave_block_sum<W>(part_d, red);
-  part_v = wave_block_sum<W>(part_v, red);
-  part_j = wave_block_sum<W>(part_j, red);
-  if (tid == 0) {
+  part_d = wave_sum(part_d);
+  part_v = wave_sum(part_v);
+  part_j = wave_sum(part_j);
+  if (vt == 0) {
     // beta log L = beta (-dt N~^-1 dt / 2 + a.d - a.S0 a / 2 + c1), with
     // beta a.S0 a = beta a.d - a.v1
     const double *k2 = S.cconst + 2 * I;
@@ -233,9 +272,9 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) v
   constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
   using E = el::Elim<T, W>;
   __shared__ el::Lds<T, W> L;
-  __shared__ double bv[2 * pp], tv[2 * pp], vk[pp], red[W];   // a then u, y = X a (sin, cos)
+  __shared__ double bv[2 * pp], tv[2 * pp], vk[pp], red[W], rho_l;   // a then u, y = X a (sin, cos)
   __shared__ int flag;
-  const int tid = threadIdx.x;
+  const int tid = el::placed_tid<W>();
   const int c = blockIdx.x / S.nf_gw, k = blockIdx.x - c * S.nf_gw;
   const int n = S.n_psr;
   const double *xc = x + (size_t)c * S.d;
@@ -244,19 +283,29 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) v
   for (int s = 0; s < E::NS; ++s) {
     // Gamma is stored as lower tiles: the slot takes rows of block C, columns
     // of block I, the transposed tile
-    const double *g = S.gam_tiles + (s * W + el.w < E::NT ? s * W + el.w : 0) * 256 + 16 * el.c + el.q;
+    const double *g = S.gam_tiles + (el.has(s) ? ps::tix(el.tile_i(s), el.tile_c(s)) : 0) * 256 + 16 * el.c + el.q;
 #pragma unroll
     for (int v = 0; v < 4; ++v) el.a[s][v] = g[4 * v];
   }
-  const double rho = ps::spec_value(S, xc, 0, 0, k);
-  for (int i = tid; i < pp; i += NTH) {
-    const double *av = S.avec + ((size_t)c * n + i) * S.pp;
-    vk[i] = (i < n) ? ((k < S.nf_rn) ? ps::spec_value(S, xc, 1, i, k) : 0.0) : 1.0;
-    bv[2 * i] = (i < n) ? av[2 * k] : 0.0;
-    bv[2 * i + 1] = (i < n) ? av[2 * k + 1] : 0.0;
+  const int vt = E::vec_tid(tid);
+  if (vt >= 0) {
+    const double r = ps::spec_value(S, xc, 0, 0, k);
+#pragma unroll
+    for (int u = 0; u < (pp + 63) / 64; ++u) {
+      const int i = vt + 64 * u;
+      if (i >= pp) break;
+      const double *av = S.avec + ((size_t)c * n + i) * S.pp;
+      vk[i] = (i < n) ? ((k < S.nf_rn) ? ps::spec_value(S, xc, 1, i, k) : 0.0) : 1.0;
+      bv[2 * i] = (i < n) ? av[2 * k] : 0.0;
+      bv[2 * i + 1] = (i < n) ? av[2 * k + 1] : 0.0;
+    }
+    if (vt == 0) {
+      flag = 1;
+      rho_l = r;
+    }
   }
-  if (tid == 0) flag = 1;
   __syncthreads();
+  const double rho = rho_l;
 #pragma unroll
   for (int s = 0; s < E::NS; ++s) {
     const bool dg = el.tile_i(s) == el.tile_c(s);
@@ -269,7 +318,7 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) v
   // row by row as X is formed: tiles (X G)_JK = sum_{M=K}^{J} X_JM G_MK
   double part_t = 0.0;
   el.template run<2, 0>(L, &flag, bv, tv, [&](int J) {
-    for (int K = (el.w + J) % W; K <= J; K += W) {
+    for (int K = (el.w + J) % E::NW; K <= J; K += E::NW) {
       v4d r{0.0, 0.0, 0.0, 0.0};
       for (int M = K; M <= J; ++M) {
         const v4d g = ldg_cm(S.gch_tiles + ps::tix(M, K) * 256, el.c, el.q);
@@ -1241,12 +1290,12 @@ __global__ __launch_bounds__(kFinT) void k_std_finalize(StdDev S, const double *
 template <int T>
 __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_split_fac(StdDev S, const double *__restrict__ x,
                                                                               int b) {
-  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  constexpr int W = elim_waves<T>(), pp = 16 * T;
   using E = el::Elim<T, W>;
   __shared__ el::Lds<T, W> L;
-  __shared__ double zv[2 * pp], va[pp], red[W];
+  __shared__ double zv[2 * pp], va[pp];
   __shared__ int flag;
-  const int tid = threadIdx.x;
+  const int tid = el::placed_tid<W>();
   const int pi = xcd_index(blockIdx.x, gridDim.x);
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
@@ -1254,50 +1303,44 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_split_f
   const int PB = b ? S.PR : S.PG;
   const size_t ci = (size_t)c * S.n_psr + I;
   E el(tid);
-  const double *s0 = (b ? S.s0r : S.s0g) + (size_t)I * pp * pp + el.q * pp + el.c;
+  load_gram<T>(el, (b ? S.s0r : S.s0g) + (size_t)I * pp * pp);
+  const int vt = E::vec_tid(tid);
+  if (vt >= 0) {
+    bool bad = false;
 #pragma unroll
-  for (int s = 0; s < E::NS; ++s) {
-    const int o = el.has(s) ? 16 * (el.tile_c(s) * pp + el.tile_i(s)) : 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) el.a[s][v] = s0[o + 4 * v * pp];
-  }
-  int bad = 0;
-  for (int r = tid; r < pp; r += NTH) {
-    zv[2 * r] = (r < PB) ? xc[S.off_z + I * S.pz + (b ? S.PG : 0) + (PB - 1 - r)] : 0.0;
-    zv[2 * r + 1] = 0.0;
-    double di = 1.0;
-    if (r < PB) {
-      const double v = ps::split_var(S, xc, I, b, PB - 1 - r);
-      if (!(v > 0.0 && isfinite(v))) bad = 1;
-      di = 1.0 / v;
+    for (int u = 0; u < (pp + 63) / 64; ++u) {
+      const int r = vt + 64 * u;
+      if (r >= pp) break;
+      zv[2 * r] = (r < PB) ? xc[S.off_z + I * S.pz + (b ? S.PG : 0) + (PB - 1 - r)] : 0.0;
+      zv[2 * r + 1] = 0.0;
+      if (r >= PB) va[r] = 1.0;
     }
-    va[r] = di;
-  }
-  bad = __syncthreads_or(bad);
-  if (tid == 0) flag = bad ? 0 : 1;
-#pragma unroll
-  for (int s = 0; s < E::NS; ++s) {
-    el.a[s] *= -beta;
-    if (el.tile_i(s) == el.tile_c(s)) {
-      const double di = va[16 * el.tile_i(s) + el.c];
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (el.q + 4 * v == el.c) el.a[s][v] -= di;
+    if (2 * vt < PB) {   // (a lane per frequency)
+      const double v = ps::split_var(S, xc, I, b, 2 * vt);
+      bad = !(v > 0.0 && isfinite(v));
+      const double di = 1.0 / v;
+      va[PB - 1 - 2 * vt] = di;
+      va[PB - 2 - 2 * vt] = di;
     }
+    bad = __any(bad);
+    if (vt == 0) flag = bad ? 0 : 1;
   }
+  __syncthreads();
+  gram_slots<T>(el, beta, va);
   __syncthreads();
   el.template run<0, 0>(L, &flag, nullptr, nullptr, [](int) {});
   double *part = L.row;
   el.xty(part, zv);
-  el::store_x(el, (b ? S.xr : S.xg) + ci * (E::NT * 256));
   __syncthreads();
+  el::store_x(el, (b ? S.xr : S.xg) + ci * (E::NT * 256));
+  if (vt < 0) return;
   double part_j = 0.0;
-  for (int r = tid; r < PB; r += NTH) {
+  for (int r = vt; r < PB; r += 64) {
     (b ? S.lzr : S.lzg)[ci * pp + (PB - 1 - r)] = el::xty_sum<T, 2>(part, 0, r);
     part_j += log(L.rs[r]);
   }
-  part_j = wave_block_sum<W>(part_j, red);
-  if (tid == 0) {
+  part_j = wave_sum(part_j);
+  if (vt == 0) {
     S.jac_s[ci * 2 + b] = part_j;
     S.flag_s[ci * 2 + b] = flag ? 0 : ps::kFlagNotPD;
   }
