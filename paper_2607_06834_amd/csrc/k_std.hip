@@ -488,8 +488,12 @@ struct ColSum {
 };
 
 // The adjoint reads all of X once (316 MB a launch at 67 pulsars x 64 chains,
-// T = 8), which bounds it: 3.3 TB/s and 95 us there; through LDS, two problems a
-// compute unit and a thread per half row and half column, it took 136.
+// T = 8), which bounds it.  It takes the problems in the reverse of the order in
+// which the forward wrote them, so that the 256 MB memory-side cache still holds
+// most of what it reads: 67 us there (4.7 TB/s), in the forward's order 95
+// (3.3 TB/s); through LDS, two problems a compute unit and a thread per half row
+// and half column, 136.  k_split_bwd likewise 73 and 106; k_split_bwd_c, whose X
+// is older than another set's, keeps the forward's order (88 us, reversed 99).
 //
 // X of one problem (block columns of 16, see el::store_x) in registers: wave w
 // of (T + 1) / 2 takes the block columns w and T - 1 - w, 4 (T + 1) values a lane
@@ -585,7 +589,7 @@ __global__ __launch_bounds__(64 * AdjX<T>::W, 4) void k_std_bwd(StdDev S, const 
   __shared__ double wp[T * pp], vv[pp], gd[pp], sg[pp];
   __shared__ double2 wz[pp];
   const int tid = threadIdx.x;
-  const int pi = xcd_index(blockIdx.x, gridDim.x);
+  const int pi = (int)gridDim.x - 1 - xcd_index(blockIdx.x, gridDim.x);   // the latest X first
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const int P = S.P;
@@ -1512,7 +1516,7 @@ __global__ __launch_bounds__(64 * AdjX<T>::W, 4) void k_split_bwd(StdDev S, cons
   __shared__ double wp[T * pp], vv[pp], gd[pp];
   __shared__ double2 wz[pp];
   const int tid = threadIdx.x;
-  const int pi = xcd_index(blockIdx.x, gridDim.x);
+  const int pi = (int)gridDim.x - 1 - xcd_index(blockIdx.x, gridDim.x);   // the latest X first
   const int I = pi / S.n_chains, c = pi - I * S.n_chains;
   const double *xc = x + (size_t)c * S.d;
   const int PB = b ? S.PR : S.PG, P = S.P;
