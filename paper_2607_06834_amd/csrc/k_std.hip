@@ -57,8 +57,15 @@ using ln::v4d;
 // 105; T = 4 for 6400, 1 wave 75, 2 waves 91; T = 7 for 900, at three waves a SIMD
 // 102, at four (six registers spilled outside of the steps) 88; T = 8 for 4288, at
 // three 254, at four 296 (142 registers spilled).
+// The prior's problems are fewer and do more at each step: T = 5 with one wave and
+// with four for 112 problems 39 and 23, for 896 63 and 50, for 3584 145 and 143;
+// T = 4 28 and 38 for 896 (and k_std_fwd<5>, 4288 problems, 78 and 96).
 template <int T>
 constexpr int elim_waves() { return T <= 5 ? 1 : 4; }
+template <int T>
+constexpr int prior_waves() { return T <= 4 ? 1 : 4; }
+template <int T>
+constexpr int prior_occ() { return T == 4 ? 2 : T == 3 || T == 8 ? 3 : 4; }
 template <int T>
 constexpr int elim_occ() { return T <= 2 || T == 6 || T == 7 ? 4 : T == 5 ? 2 : 3; }
 
@@ -267,9 +274,9 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
 // Prior per (frequency k < nf_gw, chain): phi_k = rho_k Gamma + diag kappa_.k.
 // ---------------------------------------------------------------------------
 template <int T>
-__global__ __launch_bounds__(64 * elim_waves<T>(), T == 4 ? 2 : elim_occ<T>()) void k_std_prior_dense(StdDev S,
+__global__ __launch_bounds__(64 * prior_waves<T>(), prior_occ<T>()) void k_std_prior_dense(StdDev S,
                                                                                     const double *__restrict__ x) {
-  constexpr int W = elim_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  constexpr int W = prior_waves<T>(), pp = 16 * T, NTH = 64 * W;
   using E = el::Elim<T, W>;
   __shared__ el::Lds<T, W> L;
   __shared__ double bv[2 * pp], tv[2 * pp], vk[pp], red[W], rho_l;   // a then u, y = X a (sin, cos)
@@ -1635,6 +1642,7 @@ namespace psk {
     default: return hipErrorInvalidValue;                                                    \
   }
 #define ELIM_WAVES(T) elim_waves<T>()
+#define PRIOR_WAVES(T) prior_waves<T>()
 #define ADJ_WAVES(T) AdjX<T>::W
 
 hipError_t launch_std_cw_fwd(const StdDev &S, const double *x, hipStream_t s) {
@@ -1662,7 +1670,7 @@ hipError_t launch_std_prior(const StdDev &S, const double *x, hipStream_t s) {
   if (S.nf_gw > 0) {
     const int grid = S.n_chains * S.nf_gw;
     if (S.split) hipLaunchKernelGGL(k_split_prior_g, dim3(grid), dim3(256), 0, s, S, x);
-    else PS_DISPATCH(S.tg, k_std_prior_dense, ELIM_WAVES, grid, S, x);
+    else PS_DISPATCH(S.tg, k_std_prior_dense, PRIOR_WAVES, grid, S, x);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
