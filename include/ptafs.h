@@ -189,7 +189,9 @@ int ptafs_logp_grad_plain(ptafs_dataset *ds, int32_t n_chains, const double *x, 
 /*
  * Tuning of the batched TOA pass.  tiles_per_chunk: 16-TOA tiles a workgroup
  * covers (ragged pulsars are cut into chunks of this many tiles);
- * waves_per_block: 1, 2 or 4 waves splitting a chunk; xcd_map: 0 leaves the
+ * waves_per_block: 1, 2 or 4 waves splitting a chunk (a data set whose chunks
+ * are fewer than the compute units takes up to eight a chunk, by a rule on the
+ * data set alone); xcd_map: 0 leaves the
  * work items in launch order, 1 places the chain blocks of one chunk on the
  * same XCD, 2 (balanced) also gives every compute unit chunks of near-equal
  * total TOA count when the launch is one full round of resident workgroups

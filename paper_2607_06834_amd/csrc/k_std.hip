@@ -2,7 +2,7 @@
 // standardized_stochastic_posterior in the Gram form of Eq. posterior_implemented;
 // App. B for a tempered likelihood).
 //
-// Per pulsar I and chain c (one 256-thread workgroup each):
+// Per pulsar I and chain c (one workgroup each):
 //   A = beta S0_I + diag(1 / D),  D = CURN variances of the chain (rho_k + kappa_Ik,
 //   kappa_dm,Ik);  Sigma = A^-1 = L L^T with L the lower Cholesky factor.
 // In the reversed index order r = P - 1 - j the matrix A~ = J A J has a lower
@@ -30,15 +30,14 @@
 // waveform's derivative.
 //
 // X = L~^-1 is formed by block Gauss-Jordan elimination with the matrix in the
-// registers of one to four waves (elim_dev.h), which carries t = X beta d~ and
+// registers of one to three waves (elim_dev.h), which carries t = X beta d~ and
 // L~ z~ along.  What bounds it: at 67 pulsars x 64 chains (T = 8) the products of
-// a problem take 57e3 cycles of a matrix core, a quarter of that on each of the
-// four SIMDs, and the vector instructions around them (half of them in the
-// diagonal tiles) as long again on the FP64 pipe they share; k_std_fwd<8> runs
-// at 41% of the matrix cores' cycles.  The earlier form, with the tiles in LDS
-// (two problems a compute unit, every operand and result through LDS), took 525 us
-// a launch where this takes 320, 335 where this takes 84 at 100 pulsars with
-// T = 4, and k_split_fac<8> 466 where this takes 297.
+// a problem take 57e3 cycles of a matrix core, a third of that on each of three
+// SIMDs; k_std_fwd<8> runs at half of the matrix cores' cycles there, held by what
+// elim_dev.h says, and X goes to memory (309 MB, 68 us).  The earlier form, with
+// the tiles in LDS (two problems a compute unit, every operand and result through
+// LDS), took 525 us a launch where this takes 253, 335 where this takes 84 at 100
+// pulsars with T = 4, and k_split_fac<8> 466 where this takes 236.
 #include <cmath>
 
 #include "cw_dev.h"
@@ -53,8 +52,7 @@ using ln::v4d;
 // Waves per (pulsar, chain) or (frequency, chain) elimination of T tiles, and the
 // waves a SIMD that its registers are held to.  One wave takes at most 15 tiles
 // (120 of its registers); from T = 6 three waves share them and a fourth takes the
-// diagonal tiles.  Measured, us: T = 5 for 4288 problems, 1 wave 95 and 2 waves
-// 105; T = 4 for 6400, 1 wave 75, 2 waves 91; T = 7 for 900, at three waves a SIMD
+// diagonal tiles.  Measured, us: T = 7 for 900, at three waves a SIMD
 // 102, at four (six registers spilled outside of the steps) 88; T = 8 for 4288, at
 // three 254, at four 296 (142 registers spilled).
 // The prior's problems are fewer and do more at each step: T = 5 with one wave and
@@ -108,28 +106,6 @@ __device__ inline double block_sum(double v, double *red) {
 __device__ inline int xcd_index(int b, int n) {
   const int x = b & 7, k = b >> 3, q = n >> 3, rm = n & 7;
   return x * q + (x < rm ? x : rm) + k;
-}
-
-// Block sum of three values per thread (256 threads) in one pass; red: 12
-// doubles of LDS.  Every thread gets the three sums.
-__device__ inline void block_sum3(double &a, double &b, double &c, double *red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    a += __shfl_xor(a, o, 64);
-    b += __shfl_xor(b, o, 64);
-    c += __shfl_xor(c, o, 64);
-  }
-  const int tid = threadIdx.x;
-  __syncthreads();
-  if ((tid & 63) == 0) {
-    red[tid >> 6] = a;
-    red[4 + (tid >> 6)] = b;
-    red[8 + (tid >> 6)] = c;
-  }
-  __syncthreads();
-  a = (red[0] + red[1]) + (red[2] + red[3]);
-  b = (red[4] + red[5]) + (red[6] + red[7]);
-  c = (red[8] + red[9]) + (red[10] + red[11]);
 }
 
 // sum over a wave
@@ -500,7 +476,8 @@ struct ColSum {
 // most of what it reads: 67 us there (4.7 TB/s), in the forward's order 95
 // (3.3 TB/s); through LDS, two problems a compute unit and a thread per half row
 // and half column, 136.  k_split_bwd likewise 73 and 106; k_split_bwd_c, whose X
-// is older than another set's, keeps the forward's order (88 us, reversed 99).
+// is older than another set's, finds little of it in either order (98 us; 88 with
+// k_split_bwd in the forward's order).
 //
 // X of one problem (block columns of 16, see el::store_x) in registers: wave w
 // of (T + 1) / 2 takes the block columns w and T - 1 - w, 4 (T + 1) values a lane

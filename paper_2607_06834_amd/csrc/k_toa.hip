@@ -324,11 +324,16 @@ void k_toa_mfma(Dev D, int xcd_map) {
       }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < ROWS * 16; e += 64 * WPB) {
-      double s = ftab[0][e];
+    // (with eight waves all of them add: few workgroups, and this is on their
+    // path; with four, wave 0 alone is 0.5 % of the launch faster)
+    constexpr int NADD = WPB == 8 ? 64 * WPB : 64;
+    if (WPB == 8 || wv == 0) {
+      for (int e = WPB == 8 ? (int)threadIdx.x : lane; e < ROWS * 16; e += NADD) {
+        double s = ftab[0][e];
 #pragma unroll
-      for (int w = 1; w < WPB; ++w) s += ftab[w][e];
-      pr[e] = s;
+        for (int w = 1; w < WPB; ++w) s += ftab[w][e];
+        pr[e] = s;
+      }
     }
     if (wv == 0) {
       if (lane < 16) {
@@ -357,11 +362,13 @@ void k_toa_mfma(Dev D, int xcd_map) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) ftab[wv][(16 * t + q + 4 * v) * 16 + col] = ad[t][v];
       __syncthreads();
-      for (int e = threadIdx.x; e < 16 * JTD * 16; e += 64 * WPB) {
-        double s = ftab[0][e];
+      if (WPB == 8 || wv == 0) {
+        for (int e = WPB == 8 ? (int)threadIdx.x : lane; e < 16 * JTD * 16; e += NADD) {
+          double s = ftab[0][e];
 #pragma unroll
-        for (int w = 1; w < WPB; ++w) s += ftab[w][e];
-        pd[e] = s;
+          for (int w = 1; w < WPB; ++w) s += ftab[w][e];
+          pd[e] = s;
+        }
       }
     }
   }

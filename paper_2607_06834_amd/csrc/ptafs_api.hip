@@ -297,17 +297,19 @@ void build_chunks(ptafs_dataset *ds, std::vector<int32_t> &tab) {
 
 // Waves per workgroup of the TOA pass: the tuning's, and up to eight for a data
 // set whose chunks would otherwise have fewer waves than there are compute
-// units (in one block of 16 chains: the rule must not look at the number of
-// chains, on which a chain's result does not depend), as long as every wave of
+// units by half (in one block of 16 chains: the rule must not look at the number
+// of chains, on which a chain's result does not depend), as long as every wave of
 // the longest chunk has a tile.  The chunk's waves are combined in LDS, so
 // neither the chunks nor the partials change.  Three pulsars of 500 TOAs (6
 // chunks of 16 tiles): 14.4 us a launch with one wave a chunk, 6.9 with eight;
 // with a continuous wave (33 chains) 20 and 12.8.  Beyond that line more waves
-// cost: 192 chunks of 67 pulsars at 64 chains take 13 us more with eight waves
-// than with the four they are tuned to.
+// cost where there are many chains: 22 pulsars of 750 TOAs, 193 chains and chunks
+// cut to fill the device (about 150), 123 us an evaluation with one wave a chunk,
+// 126 with two; 192 chunks of 67 pulsars at 64 chains take 13 us more with eight
+// waves than with the four they are tuned to.
 int toa_waves(const ptafs_dataset *ds) {
   int w = ds->wpb;
-  while (w < 8 && 2 * w <= ds->max_chunk_tiles && w * ds->n_chunks < ds->base.n_cu) w *= 2;
+  while (w < 8 && 2 * w <= ds->max_chunk_tiles && 2 * w * ds->n_chunks < ds->base.n_cu) w *= 2;
   return w;
 }
 
