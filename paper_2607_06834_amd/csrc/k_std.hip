@@ -247,12 +247,76 @@ __global__ __launch_bounds__(64 * elim_waves<T>(), elim_occ<T>()) void k_std_fwd
 }
 
 // ---------------------------------------------------------------------------
+// Prior of the diagonal items: red-noise frequencies beyond the common process
+// (phi_k = diag kappa_.k) and DM (diag kappa_dm): one thread per (chain, pulsar,
+// item), items k in [nf_gw, ka) then the DM frequencies.  With split
+// coefficients: the whole pulsar-noise set a_R, items k < nf_rn then DM.  With a
+// common process they are workgroups after its problems in the same launch (the
+// two write different entries, and they run on what the problems leave free).  In
+// a launch of their own they took 5 to 8 us, a tenth of an evaluation of 20 pulsars
+// x 8 chains (ten leapfrogs 461 us, so 436); the dense launch is 1 us longer for
+// them at 67 pulsars x 64 chains, k_split_prior_g 2.5.
+// ---------------------------------------------------------------------------
+__device__ inline size_t prior_diag_items(const StdDev &S) {
+  return (size_t)S.n_chains * S.n_psr * ((S.split ? S.nf_rn : S.ka - S.nf_gw) + S.kdm);
+}
+__device__ __forceinline__ void prior_diag_item(const StdDev S, const double *__restrict__ x, size_t e) {
+  const int k0 = S.split ? 0 : S.nf_gw;
+  const int nrn = S.split ? S.nf_rn : S.ka - S.nf_gw, per = nrn + S.kdm;
+  const int it = (int)(e % per);
+  const size_t ci = e / per;
+  const int I = (int)(ci % S.n_psr), c = (int)(ci / S.n_psr);
+  const double *xc = x + (size_t)c * S.d;
+  int k, col;
+  double kap;
+  if (it < nrn) {
+    k = k0 + it;
+    col = 2 * k;
+    kap = ps::spec_value(S, xc, 1, I, k);
+  } else {
+    k = it - nrn;
+    col = (S.split ? 2 * S.nf_rn : 2 * S.ka) + 2 * k;   // row in a_R, or in a
+    kap = ps::spec_value(S, xc, 2, I, k);
+  }
+  const double *av = S.split ? S.ar + ci * S.ppr : S.avec + ci * S.pp;
+  const double a0 = av[col], a1 = av[col + 1];
+  const double ik = 1.0 / kap;
+  const double u0 = a0 * ik, u1 = a1 * ik;
+  double *v2 = S.split ? S.v2r + ci * S.ppr : S.v2 + ci * S.pp;
+  v2[col] = -u0;
+  v2[col + 1] = -u1;
+  const double dk = 0.5 * (u0 * u0 + u1 * u1) - ik;
+  if (it < nrn) S.dkap_e[((size_t)c * S.n_psr + I) * S.ka + k] = dk;
+  else S.ddm_e[((size_t)c * S.n_psr + I) * S.kdm + k] = dk;
+  double *o = S.diag_q + (((size_t)c * S.n_psr + I) * (S.ka + S.kdm) + (it < nrn ? k : S.ka + k)) * 2;
+  o[0] = a0 * u0 + a1 * u1;
+  o[1] = log(kap);
+  S.flag3[((size_t)c * S.n_psr + I) * (S.ka + S.kdm) + (it < nrn ? k : S.ka + k)] =
+      ((kap > 0.0) && isfinite(kap)) ? 0 : ps::kFlagNotPD;
+}
+
+__global__ __launch_bounds__(256) void k_std_prior_diag(StdDev S, const double *__restrict__ x) {
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (e < prior_diag_items(S)) prior_diag_item(S, x, e);
+}
+
+// the workgroups of NTH threads after the n_dense ones of a launch
+template <int NTH>
+__device__ __forceinline__ bool prior_diag_group(const StdDev &S, const double *__restrict__ x, int n_dense) {
+  if ((int)blockIdx.x < n_dense) return false;
+  const size_t e = (size_t)(blockIdx.x - n_dense) * NTH + threadIdx.x;
+  if (e < prior_diag_items(S)) prior_diag_item(S, x, e);
+  return true;
+}
+
+// ---------------------------------------------------------------------------
 // Prior per (frequency k < nf_gw, chain): phi_k = rho_k Gamma + diag kappa_.k.
 // ---------------------------------------------------------------------------
 template <int T>
 __global__ __launch_bounds__(64 * prior_waves<T>(), prior_occ<T>()) void k_std_prior_dense(StdDev S,
                                                                                     const double *__restrict__ x) {
   constexpr int W = prior_waves<T>(), pp = 16 * T, NTH = 64 * W;
+  if (prior_diag_group<NTH>(S, x, S.n_chains * S.nf_gw)) return;
   using E = el::Elim<T, W>;
   __shared__ el::Lds<T, W> L;
   __shared__ double bv[2 * pp], tv[2 * pp], vk[pp], red[W], rho_l;   // a then u, y = X a (sin, cos)
@@ -362,50 +426,6 @@ __global__ __launch_bounds__(64 * prior_waves<T>(), prior_occ<T>()) void k_std_p
     S.drho_e[(size_t)c * S.ka + k] = 0.5 * ugu - tr;
     S.flag2[(size_t)c * S.ka + k] = flag ? 0 : ps::kFlagNotPD;
   }
-}
-
-// ---------------------------------------------------------------------------
-// Prior of the diagonal items: red-noise frequencies beyond the common process
-// (phi_k = diag kappa_.k) and DM (diag kappa_dm): one thread per (chain, pulsar,
-// item), items k in [nf_gw, ka) then the DM frequencies.  With split
-// coefficients: the whole pulsar-noise set a_R, items k < nf_rn then DM.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_std_prior_diag(StdDev S, const double *__restrict__ x) {
-  const int k0 = S.split ? 0 : S.nf_gw;
-  const int nrn = S.split ? S.nf_rn : S.ka - S.nf_gw, per = nrn + S.kdm;
-  const size_t total = (size_t)S.n_chains * S.n_psr * per;
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= total) return;
-  const int it = (int)(e % per);
-  const size_t ci = e / per;
-  const int I = (int)(ci % S.n_psr), c = (int)(ci / S.n_psr);
-  const double *xc = x + (size_t)c * S.d;
-  int k, col;
-  double kap;
-  if (it < nrn) {
-    k = k0 + it;
-    col = 2 * k;
-    kap = ps::spec_value(S, xc, 1, I, k);
-  } else {
-    k = it - nrn;
-    col = (S.split ? 2 * S.nf_rn : 2 * S.ka) + 2 * k;   // row in a_R, or in a
-    kap = ps::spec_value(S, xc, 2, I, k);
-  }
-  const double *av = S.split ? S.ar + ci * S.ppr : S.avec + ci * S.pp;
-  const double a0 = av[col], a1 = av[col + 1];
-  const double ik = 1.0 / kap;
-  const double u0 = a0 * ik, u1 = a1 * ik;
-  double *v2 = S.split ? S.v2r + ci * S.ppr : S.v2 + ci * S.pp;
-  v2[col] = -u0;
-  v2[col + 1] = -u1;
-  const double dk = 0.5 * (u0 * u0 + u1 * u1) - ik;
-  if (it < nrn) S.dkap_e[((size_t)c * S.n_psr + I) * S.ka + k] = dk;
-  else S.ddm_e[((size_t)c * S.n_psr + I) * S.kdm + k] = dk;
-  double *o = S.diag_q + (((size_t)c * S.n_psr + I) * (S.ka + S.kdm) + (it < nrn ? k : S.ka + k)) * 2;
-  o[0] = a0 * u0 + a1 * u1;
-  o[1] = log(kap);
-  S.flag3[((size_t)c * S.n_psr + I) * (S.ka + S.kdm) + (it < nrn ? k : S.ka + k)] =
-      ((kap > 0.0) && isfinite(kap)) ? 0 : ps::kFlagNotPD;
 }
 
 // ---------------------------------------------------------------------------
@@ -1461,6 +1481,7 @@ __global__ __launch_bounds__(kCombT, 4) void k_split_comb(StdDev S, const double
 // rho_k, ln det = N_p ln rho_k + ln det Gamma, -u / rho_k into v2 and the
 // explicit derivative (a_s^T u_s + a_c^T u_c) / (2 rho_k^2) - N_p / rho_k.
 __global__ __launch_bounds__(256) void k_split_prior_g(StdDev S, const double *__restrict__ x) {
+  if (prior_diag_group<256>(S, x, S.n_chains * S.nf_gw)) return;
   __shared__ double as[2][16 * ps::kMaxTiles];
   __shared__ double red[4];
   const int tid = threadIdx.x;
@@ -1644,16 +1665,17 @@ hipError_t launch_std_fwd(const StdDev &S, const double *x, hipStream_t s) {
 }
 
 hipError_t launch_std_prior(const StdDev &S, const double *x, hipStream_t s) {
-  if (S.nf_gw > 0) {
-    const int grid = S.n_chains * S.nf_gw;
-    if (S.split) hipLaunchKernelGGL(k_split_prior_g, dim3(grid), dim3(256), 0, s, S, x);
-    else PS_DISPATCH(S.tg, k_std_prior_dense, PRIOR_WAVES, grid, S, x);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   const size_t items =
       (size_t)S.n_chains * S.n_psr * ((S.split ? S.nf_rn : S.ka - S.nf_gw) + S.kdm);
-  if (items) hipLaunchKernelGGL(k_std_prior_diag, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, S, x);
+  if (S.n_chains > 0 && S.nf_gw > 0) {   // the diagonal items after the dense problems
+    const int nd = S.n_chains * S.nf_gw, nth = S.split || S.tg > 4 ? 256 : 64;
+    static_assert(prior_waves<4>() == 1 && prior_waves<5>() == 4, "threads of a workgroup by tiles");
+    const int grid = nd + (int)((items + nth - 1) / nth);
+    if (S.split) hipLaunchKernelGGL(k_split_prior_g, dim3(grid), dim3(256), 0, s, S, x);
+    else PS_DISPATCH(S.tg, k_std_prior_dense, PRIOR_WAVES, grid, S, x);
+  } else if (items) {
+    hipLaunchKernelGGL(k_std_prior_diag, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, S, x);
+  }
   return hipGetLastError();
 }
 
