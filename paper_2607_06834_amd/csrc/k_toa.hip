@@ -63,6 +63,7 @@ void k_toa_mfma(Dev D, int xcd_map) {
   constexpr int ROWS = 16 * JTR;
   constexpr int FS = ROWS + 1;                 // padded LDS row stride (doubles)
   constexpr bool SHB = WPB >= 4;
+  static_assert(16 * WPB + 15 <= pt::kToaPad, "the load one tile ahead stays in the per-TOA arrays");
   __shared__ double ftab[WPB][16 * FS];
   __shared__ double cred[WPB][16];
   __shared__ double cwred[CW ? WPB : 1][8][16];

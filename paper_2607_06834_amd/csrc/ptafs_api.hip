@@ -260,57 +260,28 @@ bool balanced_map(const std::vector<int32_t> &cbg, const std::vector<int32_t> &c
 // has their shape.
 void build_chunks(ptafs_dataset *ds, std::vector<int32_t> &tab) {
   const int n = ds->base.n_psr;
-  const int tpc = std::max(1, ds->tiles_per_chunk);
-  std::vector<int32_t> cps, cbg, cen;
-  std::vector<int32_t> first(n + 1, 0);
+  const pt::ToaChunks c = pt::cut_chunks(ds->off.data(), n, std::max(1, ds->tiles_per_chunk));
   ds->psr_nchunks.assign(n, 0);
-  for (int p = 0; p < n; ++p) {
-    const int64_t b = ds->off[p], e = ds->off[p + 1];
-    const int64_t tiles = (e - b + 15) / 16;
-    const int64_t nch = std::max<int64_t>(1, (tiles + tpc - 1) / tpc);
-    first[p] = (int32_t)cps.size();
-    for (int64_t i = 0; i < nch; ++i) {
-      const int64_t t0 = (i * tiles) / nch, t1 = ((i + 1) * tiles) / nch;
-      cps.push_back(p);
-      cbg.push_back((int32_t)(b + 16 * t0));
-      cen.push_back((int32_t)std::min<int64_t>(e, b + 16 * t1));
-    }
-    ds->psr_nchunks[p] = (int)nch;
-  }
-  first[n] = (int32_t)cps.size();
-  ds->n_chunks = (int)cps.size();
-  ds->max_chunk_tiles = 0;
-  for (size_t i = 0; i < cbg.size(); ++i) ds->max_chunk_tiles = std::max(ds->max_chunk_tiles, (cen[i] - cbg[i] + 15) / 16);
+  for (int p = 0; p < n; ++p) ds->psr_nchunks[p] = c.first[p + 1] - c.first[p];
+  ds->n_chunks = (int)c.psr.size();
+  ds->max_chunk_tiles = c.max_tiles;
   tab.clear();
-  tab.insert(tab.end(), cps.begin(), cps.end());
-  tab.insert(tab.end(), cbg.begin(), cbg.end());
-  tab.insert(tab.end(), cen.begin(), cen.end());
-  tab.insert(tab.end(), first.begin(), first.end());
+  tab.insert(tab.end(), c.psr.begin(), c.psr.end());
+  tab.insert(tab.end(), c.begin.begin(), c.begin.end());
+  tab.insert(tab.end(), c.end.begin(), c.end.end());
+  tab.insert(tab.end(), c.first.begin(), c.first.end());
   ds->wgmap_off.assign(kMaxMapCb + 1, -1);
   std::vector<int32_t> map;
   for (int ncb = 1; ncb <= kMaxMapCb; ++ncb)
-    if (balanced_map(cbg, cen, ncb, ds->base.n_cu, ds->base.n_xcd, map)) {
+    if (balanced_map(c.begin, c.end, ncb, ds->base.n_cu, ds->base.n_xcd, map)) {
       ds->wgmap_off[ncb] = (int)tab.size();
       tab.insert(tab.end(), map.begin(), map.end());
     }
 }
 
-// Waves per workgroup of the TOA pass: the tuning's, and up to eight for a data
-// set whose chunks would otherwise have fewer waves than there are compute
-// units by half (in one block of 16 chains: the rule must not look at the number
-// of chains, on which a chain's result does not depend), as long as every wave of
-// the longest chunk has a tile.  The chunk's waves are combined in LDS, so
-// neither the chunks nor the partials change.  Three pulsars of 500 TOAs (6
-// chunks of 16 tiles): 14.4 us a launch with one wave a chunk, 6.9 with eight;
-// with a continuous wave (33 chains) 20 and 12.8.  Beyond that line more waves
-// cost where there are many chains: 22 pulsars of 750 TOAs, 193 chains and chunks
-// cut to fill the device (about 150), 123 us an evaluation with one wave a chunk,
-// 126 with two; 192 chunks of 67 pulsars at 64 chains take 13 us more with eight
-// waves than with the four they are tuned to.
+// waves per workgroup of the TOA pass
 int toa_waves(const ptafs_dataset *ds) {
-  int w = ds->wpb;
-  while (w < 8 && 2 * w <= ds->max_chunk_tiles && 2 * w * ds->n_chunks < ds->base.n_cu) w *= 2;
-  return w;
+  return pt::toa_waves(ds->wpb, ds->max_chunk_tiles, ds->n_chunks, ds->base.n_cu);
 }
 
 // A captured trajectory graph holds the addresses of the chunk table, the
