@@ -204,8 +204,10 @@ struct NoSink {
 // Thread index of a workgroup of W = 4 waves numbered by the SIMD they run on, so
 // that wave 3 of every workgroup is on the same one (the four waves of a
 // workgroup are placed on the four SIMDs in turn, from any of them); numbered as
-// launched if two waves share a SIMD.  Only which wave does what depends on it.
-// Has a barrier; all threads call it.
+// launched if two waves share a SIMD.  Which SIMD the first wave gets differs from
+// workgroup to workgroup, so whatever is shared among the waves and put together
+// again goes by this index, not by threadIdx.x: then only which wave does what
+// depends on the placement.  Has a barrier; all threads call it.
 template <int W>
 __device__ __forceinline__ int placed_tid() {
   static_assert(W == 1 || W == 4, "one wave or one per SIMD");

@@ -73,13 +73,14 @@ __device__ inline v4d ldg_cm(const double *t, int c, int q) {
   return v4d{p[0], p[64], p[128], p[192]};
 }
 
-// Block sum of one value per thread (W waves); every thread gets the sum.
+// Block sum of one value per thread (W waves); every thread gets the sum.  tid is
+// the index by which the threads share the work (placed_tid): the waves' parts
+// are added in its order, whichever SIMDs they run on.
 template <int W>
-__device__ inline double wave_block_sum(double v, double *red) {
+__device__ inline double wave_block_sum(double v, double *red, int tid) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   if (W == 1) return v;
-  const int tid = threadIdx.x;
   __syncthreads();
   if ((tid & 63) == 0) red[tid >> 6] = v;
   __syncthreads();
@@ -408,10 +409,10 @@ __global__ __launch_bounds__(64 * prior_waves<T>(), prior_occ<T>()) void k_std_p
       part_g += s * bv[2 * i + h];
     }
   }
-  const double quad = wave_block_sum<W>(part_q, red);
-  const double ldet = wave_block_sum<W>(part_l, red);
-  const double ugu = wave_block_sum<W>(part_g, red);
-  const double tr = wave_block_sum<W>(part_t, red);
+  const double quad = wave_block_sum<W>(part_q, red, tid);
+  const double ldet = wave_block_sum<W>(part_l, red, tid);
+  const double ugu = wave_block_sum<W>(part_g, red, tid);
+  const double tr = wave_block_sum<W>(part_t, red, tid);
   for (int i = tid; i < n; i += NTH) {
     const double u0 = bv[2 * i], u1 = bv[2 * i + 1];
     S.dkap_e[((size_t)c * n + i) * S.ka + k] = 0.5 * (u0 * u0 + u1 * u1) - vk[i];
