@@ -145,7 +145,9 @@ struct Diag {
     constexpr int kPositive = 0x100 | 0x80;   // class: normal or denormal above zero
     const bool o1 = c & 1, o2 = c & 2;        // i = c mod 4
     double s = n[b], f = e[b];
+    if (b > 0) ln::wave_sync();   // the strip before has read its block
     scr[16 * q + c] = s;
+    ln::wave_sync();
     const double2 *m = reinterpret_cast<const double2 *>(scr) + 2 * b;   // minus the block, two by two
     const double2 r0 = m[0], r1 = m[8], r2 = m[16], r3 = m[24], r2b = m[17], r3b = m[25];
     // l_4 D l_4^T of the block, then the inverse of the unit lower l_4
@@ -410,7 +412,10 @@ struct Elim {
         double *o = L.row + kTile * (I + C - J);
         st_cm(o, c, q, r);
         if constexpr (Sink::kOn)
-          if (C == J) sink.below(I, J, ld_rm(o, c, q));
+          if (C == J) {
+            ln::wave_sync();
+            sink.below(I, J, ld_rm(o, c, q));
+          }
         a[s] = r;
         if (C == J) a[s] = v4d{0.0, 0.0, 0.0, 0.0};   // Y_IJ starts in step 3
       }
