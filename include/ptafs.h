@@ -189,9 +189,7 @@ int ptafs_logp_grad_plain(ptafs_dataset *ds, int32_t n_chains, const double *x, 
 /*
  * Tuning of the batched TOA pass.  tiles_per_chunk: 16-TOA tiles a workgroup
  * covers (ragged pulsars are cut into chunks of this many tiles);
- * waves_per_block: 1, 2 or 4 waves splitting a chunk (a data set whose chunks
- * are fewer than the compute units takes up to eight a chunk, by a rule on the
- * data set alone); xcd_map: 0 leaves the
+ * waves_per_block: 1, 2 or 4 waves splitting a chunk; xcd_map: 0 leaves the
  * work items in launch order, 1 places the chain blocks of one chunk on the
  * same XCD, 2 (balanced) also gives every compute unit chunks of near-equal
  * total TOA count when the launch is one full round of resident workgroups
@@ -202,6 +200,13 @@ int ptafs_logp_grad_plain(ptafs_dataset *ds, int32_t n_chains, const double *x, 
  * Takes effect on the next call; a new chunk length waits on the host for the
  * data set's own previous work and rebuilds the chunk table on the library's
  * stream.
+ * Until ptafs_set_tuning is called a data set has chunks of 16 tiles, placement
+ * 1 and one wave a chunk, or 2, 4 or 8 where its chunks are few (less than a third
+ * of the compute units) and long enough: a rule on the chunks and the number of
+ * compute units, so the order of the sums, and with it the last bits, is the
+ * same on every call and for any number of chains, but not on a device with
+ * other compute units.  ptafs_get_tuning reports 16, 1, 1 then; setting those
+ * values asks for one wave.
  */
 int ptafs_set_tuning(ptafs_dataset *ds, int32_t tiles_per_chunk, int32_t waves_per_block,
                      int32_t xcd_map);

@@ -30,6 +30,7 @@ struct ptafs_dataset {
   hipEvent_t done = nullptr;          // recorded after the data set's last enqueued work
   // tuning and chunk table of the TOA pass
   int max_chunk_tiles = 0;
+  bool tuned = false;                 // by ptafs_set_tuning
   int tiles_per_chunk = kDefaultTilesPerChunk, wpb = 1, xcd_map = 1;
   bool chunks_dirty = true;
   int32_t *d_chunk = nullptr;
@@ -281,7 +282,7 @@ void build_chunks(ptafs_dataset *ds, std::vector<int32_t> &tab) {
 
 // waves per workgroup of the TOA pass
 int toa_waves(const ptafs_dataset *ds) {
-  return pt::toa_waves(ds->wpb, ds->max_chunk_tiles, ds->n_chunks, ds->base.n_cu);
+  return pt::toa_waves(ds->tuned, ds->wpb, ds->max_chunk_tiles, ds->n_chunks, ds->base.n_cu);
 }
 
 // A captured trajectory graph holds the addresses of the chunk table, the
@@ -869,6 +870,7 @@ int ptafs_set_tuning(ptafs_dataset *ds, int32_t tiles_per_chunk, int32_t waves_p
   if (tiles_per_chunk != ds->tiles_per_chunk) ds->chunks_dirty = true;
   ds->tiles_per_chunk = tiles_per_chunk;
   ds->wpb = waves_per_block;
+  ds->tuned = true;
   ds->xcd_map = xcd_map;
   PT_TRY(hipSetDevice(ds->device));
   return ensure_chunks(ds, ds->aux);
@@ -1016,7 +1018,7 @@ int ptafs_hmc_run(ptafs_dataset *ds, int32_t n_chains, int32_t n_traj, int32_t n
   key.invalid = n_invalid;
   key.seed = seed;
   key.tiles = ds->tiles_per_chunk;
-  key.wpb = ds->wpb;
+  key.wpb = toa_waves(ds);
   key.xcd = ds->xcd_map;
   key.ws = ds->ws;
   key.hmc = ds->hmc;

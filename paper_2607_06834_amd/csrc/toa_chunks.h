@@ -41,22 +41,28 @@ inline ToaChunks cut_chunks(const int64_t *off, int n_psr, int tpc) {
   return c;
 }
 
-// Waves per workgroup of the TOA pass: the tuning's, and up to eight for a data
-// set whose chunks would otherwise have fewer waves than there are compute
-// units by half (in one block of 16 chains: the rule must not look at the number
-// of chains, on which a chain's result does not depend), as long as every wave of
-// the longest chunk has a tile.  The chunk's waves are combined in LDS, so
-// neither the chunks nor the partials change.  Three pulsars of 500 TOAs (6
-// chunks of 16 tiles): 14.4 us a launch with one wave a chunk, 6.9 with eight;
-// with a continuous wave (33 chains) 20 and 12.8.  Beyond that line more waves
-// cost where there are many chains: 22 pulsars of 750 TOAs, 193 chains and chunks
-// cut to fill the device (about 150), 123 us an evaluation with one wave a chunk,
-// 126 with two; 192 chunks of 67 pulsars at 64 chains take 13 us more with eight
-// waves than with the four they are tuned to.
-inline int toa_waves(int tuned, int max_chunk_tiles, int n_chunks, int n_cu) {
-  int w = tuned;
-  while (w < kToaMaxWaves && 2 * w <= max_chunk_tiles && 2 * w * n_chunks < n_cu) w *= 2;
-  return w;
+// Waves per workgroup of the TOA pass: those that ptafs_set_tuning gave (tuned), or
+// without it one, and more for a data set of few and long chunks.  The chunk's
+// waves are combined in LDS, so neither the chunks nor the partials change.  The
+// rule does not look at the number of chains, on which a chain's result does not
+// depend: its lines lie where up to 256 chains are not slower for it, by 256
+// compute units.  Microseconds a launch at 16, 128 and 256 chains with 1, 2, 4 and
+// 8 waves a chunk, 30 harmonics with DM:
+//   chunks of 16 tiles:   6   41 26 20 17   42 26 20 18   42 27 21 18
+//                        31   41 26 20 17   43 28 22 19   46 43 30 33
+//                        63   41 27 20 18   45 44 30 32   78 47 61 58
+//                        80   42 27 21 18   46 45 39 45   78 67 63 72
+//                       127   42 27 21 18   77 47 60 58   82 92 96 107
+//              8 tiles:  31   24 17 15 13   26 19 17 15   27 27 24 26
+//                        80   25 18 16 14   27 28 27 33   45 47 45 51
+//              4 tiles:  16   15 13 13      16 13 14      16 14 14
+//                        63   15 13 14      18 19 17      27 22 30
+// Beyond 256 chains more waves still gain with 16 chunks (1024 chains: 78 with one,
+// 59 with eight) and cost with 31 (82, 110).
+inline int toa_waves(bool tuned, int waves, int max_chunk_tiles, int n_chunks, int n_cu) {
+  if (tuned) return waves;
+  if (max_chunk_tiles >= 8) return 8 * n_chunks < n_cu ? 8 : 3 * n_chunks < n_cu ? 4 : 1;
+  return max_chunk_tiles >= 4 && 16 * n_chunks <= n_cu ? 2 : 1;
 }
 
 }  // namespace pt

@@ -21,8 +21,8 @@ extern "C" int chunks(const int64_t *off, int n, int tpc, int32_t *begin, int32_
   *max_tiles = c.max_tiles;
   return (int)c.psr.size();
 }
-extern "C" int waves(int tuned, int max_tiles, int n_chunks, int n_cu) {
-  return pt::toa_waves(tuned, max_tiles, n_chunks, n_cu);
+extern "C" int waves(int tuned, int waves, int max_tiles, int n_chunks, int n_cu) {
+  return pt::toa_waves(tuned, waves, max_tiles, n_chunks, n_cu);
 }
 """
 
@@ -61,7 +61,7 @@ COUNTS = [[500] * 3, [497] * 3, [150], [1], [16], [17], [40, 1], [1500, 1], [204
     [[300, 16 * tiles + r] for tiles in (0, 1, 7, 8, 16, 31) for r in range(1, 17)]
 
 
-@pytest.mark.parametrize("tuned", [1, 2, 4])
+@pytest.mark.parametrize("tuned", [0, 1, 2, 4, 8])   # (0: the rule)
 @pytest.mark.parametrize("tpc", [1, 4, 9, 16, 33, 96, 4096])
 def test_loads_stay_in_the_arrays(host, tpc, tuned):
     for counts in COUNTS:
@@ -69,6 +69,21 @@ def test_loads_stay_in_the_arrays(host, tpc, tuned):
         assert b[0] == 0 and e[-1] == sum(counts) and np.all(e > b) and np.all(b[1:] == e[:-1])
         assert mt == np.max((e - b + 15) // 16) <= tpc
         for n_cu in (1, 64, 256, 1 << 20):
-            w = host.waves(tuned, mt, len(b), n_cu)
+            w = host.waves(tuned > 0, tuned or 1, mt, len(b), n_cu)
             top = max(last_read(int(tb), int(te), w) for tb, te in zip(b, e))
             assert top < sum(counts) + host.pad(), (counts, tpc, tuned, n_cu, w)
+
+
+def test_waves_rule(host):
+    """A caller's number of waves is taken as it is; the rule never gives a wave
+    less than a tile of the longest chunk, nor more than one wave to many chunks."""
+    n_cu = 256
+    for n in range(1, 300):
+        for tiles in range(1, 40):
+            for w in (1, 2, 4):
+                assert host.waves(1, w, tiles, n, n_cu) == w
+            w = host.waves(0, 1, tiles, n, n_cu)
+            assert w in (1, 2, 4, 8) and w <= tiles and (w == 1 or 3 * n < n_cu)
+    assert [host.waves(0, 1, 16, n, n_cu) for n in (6, 31, 32, 85, 86, 150)] == [8, 8, 4, 4, 1, 1]
+    assert [host.waves(0, 1, 8, n, n_cu) for n in (31, 32, 86)] == [8, 4, 1]
+    assert [host.waves(0, 1, 7, n, n_cu) for n in (16, 17)] == [2, 1] and host.waves(0, 1, 3, 2, n_cu) == 1
