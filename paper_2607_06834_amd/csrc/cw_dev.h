@@ -21,6 +21,7 @@
 
 #include "common.h"
 #include "lane_dev.h"
+#include "phase_dev.h"
 
 namespace pt {
 
@@ -103,38 +104,6 @@ __device__ inline void cw_constants(const double *th, const double *p, double ou
   cw_sky(th[0], p, s2s, c2s, sph, cph, out);
 }
 
-// sin and cos of x, |x| < 2^40 (a phase beyond has no digits left): x less the
-// nearest multiple n of pi/2 by two fused steps (the two leading doubles of
-// pi/2), then the Taylor series to r^15 and r^16 on |r| <= pi/4, whose next
-// terms are below half a unit in the last place.  The library's sincos carries
-// the reduction of arguments of any size along, most of the instructions and
-// registers of the TOA pass's CW terms.
-__device__ inline void sincos_phase(double x, double &sn, double &cs) {
-  const double n = rint(x * 0.63661977236758134308);
-  double r = fma(-n, 1.57079632679489661923, x);
-  r = fma(-n, 6.123233995736766036e-17, r);
-  const double z = r * r;
-  double ps = -1.0 / 1307674368000.0, pc = 1.0 / 20922789888000.0;
-  ps = fma(ps, z, 1.0 / 6227020800.0);
-  ps = fma(ps, z, -1.0 / 39916800.0);
-  ps = fma(ps, z, 1.0 / 362880.0);
-  ps = fma(ps, z, -1.0 / 5040.0);
-  ps = fma(ps, z, 1.0 / 120.0);
-  ps = fma(ps, z, -1.0 / 6.0);
-  pc = fma(pc, z, -1.0 / 87178291200.0);
-  pc = fma(pc, z, 1.0 / 479001600.0);
-  pc = fma(pc, z, -1.0 / 3628800.0);
-  pc = fma(pc, z, 1.0 / 40320.0);
-  pc = fma(pc, z, -1.0 / 720.0);
-  pc = fma(pc, z, 1.0 / 24.0);
-  pc = fma(pc, z, -0.5);
-  const double s = fma(r * z, ps, r), c = fma(pc, z, 1.0);
-  const int k = (int)fma(-4.0, floor(0.25 * n), n);
-  const double a = (k & 1) ? c : s, b = (k & 1) ? s : c;
-  sn = (k & 2) ? -a : a;
-  cs = (k == 1 || k == 2) ? -b : b;
-}
-
 // Per-TOA state kept between the delay and its adjoint.
 struct CwToa {
   double y, ix, dEy, dEr, alpha, s2P, c2P, h;   // 1 / (1 - y), y E'(y), y E'(y) - E
@@ -165,6 +134,7 @@ struct CwLane {
   // two exponentials.  For the adjoint, with E' = dE/dy = 5/8 u^-3 = 5/8 u^5 / (1 - y):
   // y E' - E = u^-3 (5/8 - u^3 + 3/8 u^8) = v^2 u^-3 q(u), q the quotient by (u - 1)^2,
   // again without the cancellation of the difference.
+  template <bool FAR>
   __device__ inline CwToa delay(double t) const {
     CwToa s;
     s.y = K1 * t;
@@ -185,7 +155,7 @@ struct CwLane {
     s.dEy = 0.625 * s.y * im3;
     const double qu = fma(u, fma(u, fma(u, fma(u, fma(u, fma(u, 0.375, 0.75), 1.125), 1.5), 1.875), 1.25), 0.625);
     s.dEr = v * v * im3 * qu;
-    sincos_phase(2.0 * Phi, s.s2P, s.c2P);
+    sincos_phase<FAR>(2.0 * Phi, s.s2P, s.c2P);
     const double P = -s.s2P * (1.0 + ci * ci);
     const double Q = 2.0 * s.c2P * ci;
     s.h = -s.alpha * (P * U + Q * V);

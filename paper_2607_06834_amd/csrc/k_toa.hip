@@ -55,7 +55,10 @@ __device__ inline int xcd_remap(int b, int G) {
 // workgroup the panels live in registers and the inputs alternate between two
 // register sets: two waves per SIMD, one with the CW terms.  (A single wave
 // leaves the matrix core idle about half the time.)
-template <int JTR, int JTD, int WPB, bool CW>
+//
+// FAR is for data sets whose prior box lets the CW's phase out of the range of the
+// short reduction (sincos_phase); it comes with four waves a workgroup only.
+template <int JTR, int JTD, int WPB, bool CW, bool FAR = false>
 __global__ __launch_bounds__(64 * WPB, CW ? 2 : (WPB == 4 ? 3 : 2))
 void k_toa_mfma(Dev D, int xcd_map) {
   constexpr int NSR = 4 * JTR;
@@ -225,7 +228,7 @@ void k_toa_mfma(Dev D, int xcd_map) {
       double r = cdt[v] - rr[v] - cw[v] * rd[v];
       pt::CwToa cs;
       if constexpr (CW) {
-        cs = cwl.delay(ctt[v]);
+        cs = cwl.template delay<FAR>(ctt[v]);
         r -= cs.h;
       }
       const double g = r * civ[v];
@@ -453,7 +456,7 @@ __global__ __launch_bounds__(64) void k_toa_plain(Dev D, int p) {
       double r = D.dt[ii] - R - w * Rd;
       pt::CwToa cs;
       if (cwon) {
-        cs = cwl.delay(t);
+        cs = cwl.delay<true>(t);
         r -= cs.h;
       }
       const double g = on ? r / N : 0.0;
@@ -585,7 +588,9 @@ __global__ __launch_bounds__(256) void k_reduce(Dev D) {
 template <int JTR, int JTD, int WPB>
 hipError_t launch_mfma_t(const Dev &D, int xcd, hipStream_t s) {
   const int grid = D.n_chunks * D.n_cb;
-  if (D.has_cw)
+  if (D.has_cw == 2)
+    hipLaunchKernelGGL((k_toa_mfma<JTR, JTD, 4, true, true>), dim3(grid), dim3(64 * 4), 0, s, D, xcd);
+  else if (D.has_cw)
     hipLaunchKernelGGL((k_toa_mfma<JTR, JTD, WPB, true>), dim3(grid), dim3(64 * WPB), 0, s, D, xcd);
   else
     hipLaunchKernelGGL((k_toa_mfma<JTR, JTD, WPB, false>), dim3(grid), dim3(64 * WPB), 0, s, D, xcd);

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "phase_dev.h"
 #include "pool.h"
 
 constexpr int kDefaultTilesPerChunk = 16;
@@ -518,9 +519,20 @@ int plan(const ptafs_dataset_desc *d, pt::Dev &B) {
     pc -= std::log(d->prior_hi[i] - d->prior_lo[i]);
   }
   B.prior_const = pc;
-  double tmax = 0.0;
-  for (int64_t i = 0; i < ntoa; ++i) tmax = std::max(tmax, d->t[i]);
+  double tmax = 0.0, tabs = 0.0;
+  for (int64_t i = 0; i < ntoa; ++i) {
+    tmax = std::max(tmax, d->t[i]);
+    tabs = std::max(tabs, std::fabs(d->t[i]));
+  }
   B.tmax = tmax;
+  if (B.has_cw) {
+    // |2 Phi| <= 2 (|Phi0| + 8/5 w0 |t|), as E <= |y| before the merger; a point
+    // outside the box is not evaluated
+    const double *lo = d->prior_lo + B.off_cw, *hi = d->prior_hi + B.off_cw;
+    const double w0 = pt::kPi * std::pow(10.0, hi[3]);
+    const double phase = 2.0 * (std::max(std::fabs(lo[4]), std::fabs(hi[4])) + 1.6 * w0 * tabs);
+    if (!(1.01 * phase < pt::kFarPhase)) B.has_cw = 2;
+  }
   return PTAFS_OK;
 }
 
