@@ -208,7 +208,8 @@ int ptafs_logp_grad_plain(ptafs_dataset *ds, int32_t n_chains, const double *x, 
  * other compute units.  ptafs_get_tuning reports 16, 1, 1 then; setting those
  * values asks for one wave.
  * A data set whose prior box lets the continuous wave's phase 2 Phi grow beyond
- * 2^45 rad (|Phi0| or the frequency) always takes four waves a chunk.
+ * 2^45 rad (|Phi0| or the frequency), or its evolution variable at negative times
+ * beyond -2^126, always takes four waves a chunk.
  */
 int ptafs_set_tuning(ptafs_dataset *ds, int32_t tiles_per_chunk, int32_t waves_per_block,
                      int32_t xcd_map);

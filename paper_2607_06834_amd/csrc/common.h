@@ -102,7 +102,7 @@ struct Dev {
   // sizes
   int n_psr, n_toa, n_backend;
   int nf_rn, nf_gw, nf_dm;
-  int has_cw;    // 0, 1, or 2 where the prior box lets the CW's phase reach kFarPhase
+  int has_cw;    // 0, 1, or 2 where the prior box lets the CW's phase reach kFarPhase or 1 - y 2^126
   int ka;        // coefficient frequencies max(nf_rn, nf_gw)
   int kb;        // basis harmonics of the TOA pass max(ka, nf_dm)
   int jt_rn, jt_dm, rows_rn, rows_dm;

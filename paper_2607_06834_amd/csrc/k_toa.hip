@@ -57,7 +57,8 @@ __device__ inline int xcd_remap(int b, int G) {
 // leaves the matrix core idle about half the time.)
 //
 // FAR is for data sets whose prior box lets the CW's phase out of the range of the
-// short reduction (sincos_phase); it comes with four waves a workgroup only.
+// short reduction (sincos_phase), or its evolution out of that of the 32-bit
+// estimate (CwLane::delay); it comes with four waves a workgroup only.
 template <int JTR, int JTD, int WPB, bool CW, bool FAR = false>
 __global__ __launch_bounds__(64 * WPB, CW ? 2 : (WPB == 4 ? 3 : 2))
 void k_toa_mfma(Dev D, int xcd_map) {

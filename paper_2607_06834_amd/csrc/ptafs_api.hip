@@ -519,10 +519,11 @@ int plan(const ptafs_dataset_desc *d, pt::Dev &B) {
     pc -= std::log(d->prior_hi[i] - d->prior_lo[i]);
   }
   B.prior_const = pc;
-  double tmax = 0.0, tabs = 0.0;
+  double tmax = 0.0, tabs = 0.0, tneg = 0.0;
   for (int64_t i = 0; i < ntoa; ++i) {
     tmax = std::max(tmax, d->t[i]);
     tabs = std::max(tabs, std::fabs(d->t[i]));
+    tneg = std::max(tneg, -d->t[i]);
   }
   B.tmax = tmax;
   if (B.has_cw) {
@@ -531,7 +532,8 @@ int plan(const ptafs_dataset_desc *d, pt::Dev &B) {
     const double *lo = d->prior_lo + B.off_cw, *hi = d->prior_hi + B.off_cw;
     const double w0 = pt::kPi * std::pow(10.0, hi[3]);
     const double phase = 2.0 * (std::max(std::fabs(lo[4]), std::fabs(hi[4])) + 1.6 * w0 * tabs);
-    if (!(1.01 * phase < pt::kFarPhase)) B.has_cw = 2;
+    const double k1 = 51.2 * std::pow(pt::kTsun * std::pow(10.0, hi[2]) * w0, 5.0 / 3.0) * w0;   // y = k1 t
+    if (!(1.01 * phase < pt::kFarPhase) || !(1.0 + 1.01 * k1 * tneg < 0x1p126)) B.has_cw = 2;
   }
   return PTAFS_OK;
 }
