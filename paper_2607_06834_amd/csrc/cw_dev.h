@@ -129,20 +129,20 @@ struct CwLane {
   // With u = (1 - y)^(1/8): alpha = a0 u, and since 1 - u^8 = y,
   // v = u - 1 = -y / ((1 + u)(1 + u^2)(1 + u^4)) without cancellation, and so
   // E = 1 - (1 - y)^(5/8) = 1 - (1 + v)^5 as a polynomial in v.  u comes from
-  // the 32-bit logarithm and exponential, with FAR from three estimates of the
+  // the 32-bit logarithm and exponential, with WIDE from three estimates of the
   // square root (1 - y may leave the range of 32 bits at times before zero), by one
   // step of third order (the estimate's relative error, about 1e-7, cubed).  In place of log1p, expm1 and
   // two exponentials.  For the adjoint, with E' = dE/dy = 5/8 u^-3 = 5/8 u^5 / (1 - y):
   // y E' - E = u^-3 (5/8 - u^3 + 3/8 u^8) = v^2 u^-3 q(u), q the quotient by (u - 1)^2,
   // again without the cancellation of the difference.
-  template <bool FAR>
+  template <bool FAR, bool WIDE = FAR>
   __device__ inline CwToa delay(double t) const {
     CwToa s;
     s.y = K1 * t;
     const double x = 1.0 - s.y;
     s.ix = ln::rcp_nr(x);
     double u0;
-    if constexpr (FAR) u0 = __builtin_amdgcn_sqrt(__builtin_amdgcn_sqrt(__builtin_amdgcn_sqrt(x)));
+    if constexpr (WIDE) u0 = __builtin_amdgcn_sqrt(__builtin_amdgcn_sqrt(__builtin_amdgcn_sqrt(x)));
     else u0 = (double)__builtin_amdgcn_exp2f(0.125f * __builtin_amdgcn_logf((float)x));
     double u8 = u0 * u0;
     u8 *= u8;

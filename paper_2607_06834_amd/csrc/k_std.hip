@@ -787,7 +787,7 @@ __global__ __launch_bounds__(kCwT, 4) void k_std_cw_fwd(StdDev S, const double *
   {
     const pt::CwLane L = cw_lane(cst + c * pt::kCwRows);
     for (int j = tid >> 4; j < kCwRowsMax; j += kCwT / 16)
-      hs[j * kCwLd + c] = (c < nc && j < M) ? L.delay<true>((double)j * S.td / M).h : 0.0;
+      hs[j * kCwLd + c] = (c < nc && j < M) ? L.delay<true, false>((double)j * S.td / M).h : 0.0;
   }
   Half h0, h1;
   h0.load(dft, 0);
@@ -908,7 +908,7 @@ __global__ __launch_bounds__(kCwT, 4) void k_std_cw_bwd(StdDev S, const double *
       const double *cc = cst + ch * pt::kCwRows;
       const pt::CwLane L = cw_lane(cc);
       double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      for (int j = lc; j < M; j += LC) L.adjoint(L.delay<true>((double)j * S.td / M), gb[j * kCwLd + ch], acc);
+      for (int j = lc; j < M; j += LC) L.adjoint(L.delay<true, false>((double)j * S.td / M), gb[j * kCwLd + ch], acc);
       // the sky pair through the antenna derivatives, ln 10 for the log10 parameters
       out[0] = -(cc[pt::kCwDfpC] * acc[0] + cc[pt::kCwDfxC] * acc[1]);
       out[1] = -(cc[pt::kCwDfpP] * acc[0] + cc[pt::kCwDfxP] * acc[1]);
