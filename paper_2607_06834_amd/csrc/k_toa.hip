@@ -48,19 +48,32 @@ __device__ inline int xcd_remap(int b, int G) {
 // and the per-call 1/N.
 // ---------------------------------------------------------------------------
 //
-// With four waves per workgroup (SHB) the waves share the coefficient panels
-// in LDS instead of holding them in registers, and keep one set of per-tile
-// inputs, reloaded once the residuals are formed: three waves per SIMD (two
-// with the CW terms, a few registers spilled).  With one or two waves per
+// With four or eight waves per workgroup (SHB) the waves share the coefficient
+// panels in LDS instead of holding them in registers, and keep one set of per-tile
+// inputs, reloaded once the residuals are formed.  With one or two waves per
 // workgroup the panels live in registers and the inputs alternate between two
-// register sets: two waves per SIMD, one with the CW terms.  (A single wave
-// leaves the matrix core idle about half the time.)
+// register sets.  (A single wave leaves the matrix core idle about half the time.)
 //
+// Waves a SIMD (toa_occ): three for the shared panels of four waves, else two, with
+// the CW terms two as long as the registers suffice.  From six 16-row tiles of
+// both blocks on (seven with two waves a workgroup) two waves a SIMD spill 37 to 63
+// registers a lane, and one without spills is faster, us a launch at 45 pulsars of
+// 900 to 1600 TOAs, one wave a chunk of 16 tiles, with two waves a SIMD and with
+// one:
+//   3 + 2 tiles   16 chains 50 49    64 chains 57 53     256 chains 167 178
+//   3 + 3                   61 53              103 57               198 194
+//   4 + 2                   62 54              80 59                204 200
+//   4 + 4                   77 63              99 67                259 232
+constexpr int toa_occ(int jtr, int jtd, int wpb, bool cw) {
+  if (!cw) return wpb == 4 ? 3 : 2;
+  return wpb <= 2 && jtr + jtd >= 5 + wpb ? 1 : 2;
+}
+
 // FAR is for data sets whose prior box lets the CW's phase out of the range of the
 // short reduction (sincos_phase), or its evolution out of that of the 32-bit
 // estimate (CwLane::delay); it comes with four waves a workgroup only.
 template <int JTR, int JTD, int WPB, bool CW, bool FAR = false>
-__global__ __launch_bounds__(64 * WPB, CW ? 2 : (WPB == 4 ? 3 : 2))
+__global__ __launch_bounds__(64 * WPB, toa_occ(JTR, JTD, WPB, CW))
 void k_toa_mfma(Dev D, int xcd_map) {
   constexpr int NSR = 4 * JTR;
   constexpr int NSD = 4 * JTD;
