@@ -37,7 +37,8 @@ using pt::Dev;
 using pt::pk;
 using ps::tix;
 
-constexpr int kW = 4;   // waves per problem
+constexpr int kW = 4;       // waves per problem
+constexpr int kPerCu = 2;   // problems a compute unit (one wave of each a SIMD)
 
 // the factor C of a problem: tile-major with row-major tiles up to seven
 // tiles, packed row-major beyond (chol_store_doubles)
@@ -64,13 +65,15 @@ struct FactorOut {
   }
 };
 
-// grid: nf_gw c_pad problems, then the diagonal-frequency workgroups
-template <int NT>
-__global__ __launch_bounds__(64 * kW, 2) void k_cholw_fwd(Dev D, const double *__restrict__ x, int n_dense) {
+// grid: nf_gw c_pad problems, and the diagonal-frequency workgroups after them
+// (FIRST: before)
+template <int NT, bool FIRST>
+__global__ __launch_bounds__(64 * kW, kPerCu) void k_cholw_fwd(Dev D, const double *__restrict__ x, int n_dense) {
   static_assert(64 * kW == 256, "the diagonal-frequency work runs on 256 threads");
-  if ((int)blockIdx.x >= n_dense) {
+  const int prob = FIRST ? (int)(blockIdx.x - (gridDim.x - n_dense)) : (int)blockIdx.x;
+  if (FIRST ? prob < 0 : prob >= n_dense) {
     const pt::spec_split sp(D, gridDim.x - n_dense, D.c_pad, false);
-    for (int it = blockIdx.x - n_dense; it < sp.nb * sp.ns; it += sp.G) {
+    for (int it = FIRST ? blockIdx.x : prob - n_dense; it < sp.nb * sp.ns; it += sp.G) {
       const int b = it / sp.ns, s = it - b * sp.ns;
       pt::spec_fwd_cb(D, x, b * pt::kCB, sp.k_lo(s), sp.k_lo(s + 1), s, sp.ns);
       __syncthreads();
@@ -83,7 +86,6 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_fwd(Dev D, const double *_
   __shared__ el::Lds<NT, kW> L;
   __shared__ double bv[2 * NP], tv[2 * NP], kb[NP];   // C z, z (sin, cos), kappa
   __shared__ int fail;
-  const int prob = blockIdx.x;
   const int k0 = prob % D.nf_gw, c = prob / D.nf_gw;
   const int tid = el::placed_tid<kW>();
   const int n = D.n_psr;
@@ -146,8 +148,8 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_fwd(Dev D, const double *_
 }
 
 // ---------------------------------------------------------------------------
-// Backward: grid nf_gw n_chains problems, then the diagonal-frequency
-// workgroups.
+// Backward: grid nf_gw n_chains problems, and the diagonal-frequency workgroups
+// after or before them.
 // ---------------------------------------------------------------------------
 
 // element (r, c) of an LDS tile: 16 lanes that read a row or a column hit 16 banks
@@ -163,15 +165,16 @@ __device__ inline void st_b(double *t, int c, int q, const v4d &v) {
   for (int i = 0; i < 4; ++i) t[at(4 * q + i, c)] = v[i];
 }
 
-template <int NT>
-__global__ __launch_bounds__(64 * kW, 2) void k_cholw_bwd(Dev D, const double *__restrict__ x,
+template <int NT, bool FIRST>
+__global__ __launch_bounds__(64 * kW, kPerCu) void k_cholw_bwd(Dev D, const double *__restrict__ x,
                                                           double *__restrict__ grad,
                                                           const double *__restrict__ lst,
                                                           const double *__restrict__ gch,
                                                           const double *__restrict__ bar, int n_dense) {
-  if ((int)blockIdx.x >= n_dense) {
+  const int prob = FIRST ? (int)(blockIdx.x - (gridDim.x - n_dense)) : (int)blockIdx.x;
+  if (FIRST ? prob < 0 : prob >= n_dense) {
     const pt::spec_split sp(D, gridDim.x - n_dense, D.n_chains, true);
-    for (int it = blockIdx.x - n_dense; it < sp.nb * sp.ns; it += sp.G) {
+    for (int it = FIRST ? blockIdx.x : prob - n_dense; it < sp.nb * sp.ns; it += sp.G) {
       const int b = it / sp.ns, s = it - b * sp.ns;
       pt::spec_bwd_cb(D, x, grad, b * pt::kCB, sp.k_lo(s), sp.k_lo(s + 1), s, sp.ns);
       __syncthreads();
@@ -184,7 +187,6 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_bwd(Dev D, const double *_
   __shared__ double ab[NP][2];
   __shared__ double drw[kW];
   __shared__ int nbw[kW];
-  const int prob = blockIdx.x;
   const int k0 = prob % D.nf_gw, c = prob / D.nf_gw;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, c16 = l & 15, q = l >> 4;
   const int pc = qf::pi16(c16);
@@ -395,18 +397,40 @@ __global__ __launch_bounds__(64 * kW, 2) void k_cholw_bwd(Dev D, const double *_
   }
 }
 
+// Diagonal-frequency workgroups beside dense problems that fill the device: they go
+// first, about one a compute unit.  Beside fewer they go last, on what the dense
+// ones leave free (spec_groups_fwd, spec_groups); beside more than one round they
+// would start there when the dense ones end, a few long workgroups at the end of the
+// launch.  96 pulsars, 14 common and 30 diagonal frequencies with DM, 48 and 256
+// chains: forward 54 and 253 us with them last, 50 and 169 first, adjoint 107 and
+// 328, 49 and 204.
+inline bool fills(const Dev &D, int np) { return np >= kPerCu * D.n_cu; }
+inline int groups_first(const Dev &D, int chains, int max_seg) {
+  const int nb = (chains + pt::kCB - 1) / pt::kCB, kmax = max(D.ka, D.nf_dm);
+  return nb * max(1, min(min(kmax, max_seg), D.n_cu / nb));
+}
+
 template <int NT>
 hipError_t launch_fwd_t(const Dev &D, const double *x, hipStream_t s) {
   const int np = D.nf_gw * D.c_pad;
-  hipLaunchKernelGGL(k_cholw_fwd<NT>, dim3(np + pt::spec_groups_fwd(D, np, D.c_pad)), dim3(64 * kW), 0, s, D, x, np);
+  if (fills(D, np))
+    hipLaunchKernelGGL((k_cholw_fwd<NT, true>), dim3(np + groups_first(D, D.c_pad, PTAFS_MAX_HARM)), dim3(64 * kW), 0,
+                       s, D, x, np);
+  else
+    hipLaunchKernelGGL((k_cholw_fwd<NT, false>), dim3(np + pt::spec_groups_fwd(D, np, D.c_pad)), dim3(64 * kW), 0, s, D,
+                       x, np);
   return hipGetLastError();
 }
 
 template <int NT>
 hipError_t launch_bwd_t(const Dev &D, const double *x, double *grad, hipStream_t s) {
   const int np = D.nf_gw * D.n_chains;
-  hipLaunchKernelGGL(k_cholw_bwd<NT>, dim3(np + pt::spec_groups(D, np, D.n_chains, 2)), dim3(64 * kW), 0, s, D, x,
-                     grad, (const double *)D.lstore, D.gtile, (const double *)D.bar_rn, np);
+  if (fills(D, np))
+    hipLaunchKernelGGL((k_cholw_bwd<NT, true>), dim3(np + groups_first(D, D.n_chains, pt::kSpecSeg)), dim3(64 * kW), 0,
+                       s, D, x, grad, (const double *)D.lstore, D.gtile, (const double *)D.bar_rn, np);
+  else
+    hipLaunchKernelGGL((k_cholw_bwd<NT, false>), dim3(np + pt::spec_groups(D, np, D.n_chains, kPerCu)), dim3(64 * kW),
+                       0, s, D, x, grad, (const double *)D.lstore, D.gtile, (const double *)D.bar_rn, np);
   return hipGetLastError();
 }
 
