@@ -54,7 +54,7 @@ def measured_traffic(tuning):
             k, v = line.split(":", 1)
             fields[k.strip()] = v.strip()
     m = hashlib.sha256()
-    for f in ("k_toa.hip", "common.h", "cw_dev.h"):
+    for f in ("k_toa.hip", "common.h", "toa_chunks.h", "cw_dev.h", "phase_dev.h", "lane_dev.h"):
         m.update(open(os.path.join(ROOT, "paper_2607_06834_amd", "csrc", f), "rb").read())
     if fields.get("source_sha256") != m.hexdigest() or key not in fields:
         return None
@@ -74,7 +74,7 @@ def measured_std_traffic():
             k, v = line.split(":", 1)
             fields[k.strip()] = v.strip()
     m = hashlib.sha256()
-    for f in ("k_std.hip", "std.h", "cw_dev.h", "elim_dev.h", "lane_dev.h"):
+    for f in ("k_std.hip", "std.h", "cw_dev.h", "phase_dev.h", "elim_dev.h", "lane_dev.h"):
         m.update(open(os.path.join(ROOT, "paper_2607_06834_amd", "csrc", f), "rb").read())
     key = "traffic_bytes_per_launch[k_std_fwd 67psr]"
     if fields.get("source_sha256") != m.hexdigest() or key not in fields:

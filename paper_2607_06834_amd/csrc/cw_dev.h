@@ -131,8 +131,9 @@ struct CwLane {
   // E = 1 - (1 - y)^(5/8) = 1 - (1 + v)^5 as a polynomial in v.  u comes from
   // the 32-bit logarithm and exponential, with WIDE from three estimates of the
   // square root (1 - y may leave the range of 32 bits at times before zero), by one
-  // step of third order (the estimate's relative error, about 1e-7, cubed).  In place of log1p, expm1 and
-  // two exponentials.  For the adjoint, with E' = dE/dy = 5/8 u^-3 = 5/8 u^5 / (1 - y):
+  // step of third order (the estimate's relative error, about 1e-7, cubed).  In
+  // place of log1p, expm1 and two exponentials.  For the adjoint, with
+  // E' = dE/dy = 5/8 u^-3 = 5/8 u^5 / (1 - y):
   // y E' - E = u^-3 (5/8 - u^3 + 3/8 u^8) = v^2 u^-3 q(u), q the quotient by (u - 1)^2,
   // again without the cancellation of the difference.
   template <bool FAR, bool WIDE = FAR>
