@@ -408,6 +408,7 @@ void k_toa_mfma(Dev D, int xcd_map) {
 // ---------------------------------------------------------------------------
 constexpr int kPlainMaxGroups = 8;   // 16-row groups per block (rows <= 128)
 
+template <bool FAR>
 __global__ __launch_bounds__(64) void k_toa_plain(Dev D, int p) {
   extern __shared__ double lds[];
   const int lane = threadIdx.x;
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(64) void k_toa_plain(Dev D, int p) {
       double r = D.dt[ii] - R - w * Rd;
       pt::CwToa cs;
       if (cwon) {
-        cs = cwl.delay<true>(t);
+        cs = cwl.template delay<FAR>(t);
         r -= cs.h;
       }
       const double g = on ? r / N : 0.0;
@@ -654,7 +655,8 @@ hipError_t launch_toa_plain_psr(const pt::Dev &D, int p, int n_chunks_p, hipStre
       D.rows_dm % 16)
     return hipErrorInvalidValue;
   const size_t lds = (size_t)((D.rows_rn + D.rows_dm) * 16 + 64 * 33) * sizeof(double);
-  hipLaunchKernelGGL(k_toa_plain, dim3(n_chunks_p, D.n_cb), dim3(64), lds, s, D, p);
+  if (D.has_cw == 2) hipLaunchKernelGGL(k_toa_plain<true>, dim3(n_chunks_p, D.n_cb), dim3(64), lds, s, D, p);
+  else hipLaunchKernelGGL(k_toa_plain<false>, dim3(n_chunks_p, D.n_cb), dim3(64), lds, s, D, p);
   return hipGetLastError();
 }
 
@@ -666,8 +668,9 @@ hipError_t launch_reduce_chunks(const pt::Dev &D, hipStream_t s) {
 }
 
 hipError_t set_plain_lds_limit(size_t bytes) {
-  return hipFuncSetAttribute((const void *)k_toa_plain, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)bytes);
+  const void *far = (const void *)k_toa_plain<true>, *plain = (const void *)k_toa_plain<false>;
+  const hipError_t e = hipFuncSetAttribute(far, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return e != hipSuccess ? e : hipFuncSetAttribute(plain, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 }  // namespace ptk
